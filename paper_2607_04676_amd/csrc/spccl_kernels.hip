@@ -2384,8 +2384,8 @@ __global__ void __launch_bounds__(kBlockThreads) k_to_dense_rb(DenseSinkArgs g, 
 // stores, so a read that has to be waited for after a store also waits for
 // that store; with the reads in front the writes stream and the read latency
 // is paid once per K tiles.  Tiles that do not fit are expanded one at a
-// time (stage their values, then write), and a tile holding more than
-// kChunkVals values reads its column runs per lane, 16 rows at a time.
+// time (stage their values, then write), and tiles holding more than
+// kChunkVals values by the whole block (block_tiles).
 // Rows [r0, r0 + 16) of dense tile t (bounded buffer loads, zero past n).
 template <class E>
 __device__ __forceinline__ void fetch_dense_rows16(const uint8_t* base, uint64_t t, uint64_t n, int r0,
@@ -2410,99 +2410,264 @@ __device__ __forceinline__ void fetch_dense_rows16(const uint8_t* base, uint64_t
     }
 }
 
-// One tile from the LDS stage: value of row r of this lane's column is
-// stage[rank] for its set bits, rank counting up from `rank`.  bf16 rows go
-// out with streaming stores (2.2 us faster over a 256 MiB decompress), fp32
-// rows with ordinary ones (1.5 us faster than streaming there).
+// A wave's run of dense output elements, assembled in LDS a unit (4 KiB) at a
+// time and stored in whole 128-byte lines, 16 bytes per lane.  A tile is 4096
+// consecutive elements, so however the values reach the unit (scattered by
+// column, or by flat index), it leaves as one stream.  The output need only
+// be element-aligned: element 0 of a unit sits at its line offset (shift) in
+// the buffer, and the part of a unit past its last whole line stays for the
+// next one, so only the first and last line of the wave's run are stored in
+// part.  Row-by-row stores of unaligned rows (two part lines per 128-byte
+// row) ran at 0.6 TB/s: a sliced all-gather hop of 8 x 5,000,011 bf16
+// elements took 140 us, now 50 (with block_tiles).
 template <class E>
-__device__ __forceinline__ void store_row(typename E::raw* p, typename E::raw v) {
-    if constexpr (sizeof(typename E::raw) == 2) st_stream(p, v);
-    else *p = v;
+struct LineOut {
+    using raw = typename E::raw;
+    static constexpr uint32_t kBytes = 4096, kLine = 128;
+    static constexpr uint32_t kElems = kBytes / sizeof(raw);   // elements of a unit
+    static constexpr uint32_t kRows = kElems / 64;              // tile rows of a unit
+    static constexpr uint32_t kVecs = (kBytes + kLine) / 16;    // the LDS buffer
+    uint4* buf;
+    uint8_t* line;        // where buf goes: the line that holds the unit's first element
+    uint32_t shift;       // bytes of that line before the unit
+    uint32_t lo;          // bytes of the buffer that are not this wave's to write (first unit: shift)
+
+    __device__ __forceinline__ void start(uint4* b, raw* out) {
+        const uintptr_t p = reinterpret_cast<uintptr_t>(out);
+        buf = b;
+        shift = (uint32_t)(p & (kLine - 1));
+        line = reinterpret_cast<uint8_t*>(out) - shift;
+        lo = shift;
+    }
+    // The unit all zero, after what the previous one left in its last line.
+    // (A wave's LDS operations execute in order: only the compiler must not
+    // move them.)
+    __device__ __forceinline__ raw* clear() {
+        const uint32_t l = lane_id();
+        constexpr uint4 zero{0, 0, 0, 0};
+        if (shift) {
+            uint4 carry = zero;
+            if (lo == 0 && l < kLine / 16) carry = buf[kBytes / 16 + l];
+            asm volatile("" ::: "memory");
+            if (l < kLine / 16) buf[kBytes / 16 + l] = zero;
+#pragma unroll
+            for (uint32_t k = 0; k < kBytes / 1024; k++) buf[l + 64 * k] = zero;
+            asm volatile("" ::: "memory");
+            if (l < kLine / 16) buf[l] = carry;
+        } else {
+#pragma unroll
+            for (uint32_t k = 0; k < kBytes / 1024; k++) buf[l + 64 * k] = zero;
+        }
+        asm volatile("" ::: "memory");
+        return reinterpret_cast<raw*>(reinterpret_cast<uint8_t*>(buf) + shift);
+    }
+    // Vector c of the buffer, if [lo, hi) covers it; its elements inside otherwise.
+    __device__ __forceinline__ void put(uint32_t c, uint32_t hi) {
+        const uint32_t b = 16 * c;
+        if (b >= lo && b + 16 <= hi) {
+            st_stream(reinterpret_cast<uint4*>(line) + c, buf[c]);
+        } else {
+            const raw* src = reinterpret_cast<const raw*>(buf);
+            raw* dst = reinterpret_cast<raw*>(line);
+            for (uint32_t e = b < lo ? lo : b; e < b + 16 && e < hi; e += sizeof(raw))
+                st_stream(&dst[e / sizeof(raw)], src[e / sizeof(raw)]);
+        }
+    }
+    // Stores the unit's first `elems` elements (all of them, but for the
+    // array's last unit); last: nothing of the run follows.
+    __device__ __forceinline__ void flush(uint32_t elems, bool last) {
+        const uint32_t l = lane_id();
+        const uint32_t hi = shift + elems * (uint32_t)sizeof(raw);
+        asm volatile("" ::: "memory");
+        if (lo == 0 && hi >= kBytes) {
+            uint4 x[kBytes / 1024];
+#pragma unroll
+            for (uint32_t k = 0; k < kBytes / 1024; k++) x[k] = buf[l + 64 * k];
+#pragma unroll
+            for (uint32_t k = 0; k < kBytes / 1024; k++) st_stream(reinterpret_cast<uint4*>(line) + l + 64 * k, x[k]);
+        } else {
+#pragma unroll 1
+            for (uint32_t k = 0; k < kBytes / 1024; k++) put(l + 64 * k, hi);
+        }
+        if (last && hi > kBytes && l < kLine / 16) put(kBytes / 16 + l, hi);
+        asm volatile("" ::: "memory");
+        line += kBytes;
+        lo = 0;
+    }
+};
+
+// The rows set in sub (this lane's column of a unit) from stage[rank ...] to
+// their places, two per round; returns the rank after them.
+template <class E>
+__device__ __forceinline__ uint32_t scatter_column(uint32_t sub, uint32_t rank, const typename E::raw* stage,
+                                                   typename E::raw* col) {
+    using raw = typename E::raw;
+    while (__any(sub != 0u)) {
+        if (sub) {
+            const uint32_t r = (uint32_t)__builtin_ctz(sub), nx = sub & (sub - 1u);
+            if (nx) {
+                const raw x = stage[rank], y = stage[rank + 1];
+                col[64 * r] = x;
+                col[64 * __builtin_ctz(nx)] = y;
+                rank += 2;
+            } else {
+                col[64 * r] = stage[rank];
+                rank++;
+            }
+            sub = nx & (nx - 1u);
+        }
+    }
+    return rank;
 }
 
+// One tile from the LDS stage into the run: the value of each set bit of this
+// lane's column word w is stage[rank], rank counting up.  A unit is cleared,
+// each lane writes its column's values at their rows, and the unit is stored:
+// the work follows the nonzeros, and the stores are 1 KiB per instruction.
+// (Walking all 64 rows and storing each one as it is finished took five vector
+// instructions a row at any sparsity: fp32 at 90% 57.8 -> 55.1 us for 256 MiB,
+// level at 99%, where the stores are the bound either way.)
 template <class E>
-__device__ __forceinline__ void store_from_stage(typename E::raw* col, uint64_t rem, uint64_t w,
-                                                 const typename E::raw* stage, uint32_t rank) {
+__device__ __forceinline__ void store_from_stage(LineOut<E>& out, uint64_t rem, uint64_t w, const typename E::raw* stage,
+                                                 uint32_t rank, bool last) {
     using raw = typename E::raw;
-    const uint32_t l = lane_id();
-    if (rem >= kTileElems) {
-#pragma unroll 8
-        for (int r = 0; r < 64; r++) {
-            raw v = 0;
-            if ((w >> r) & 1ull) { v = stage[rank]; rank++; }
-            store_row<E>(&col[64 * r], v);
-        }
-    } else {
-#pragma unroll 8
-        for (int r = 0; r < 64; r++) {
-            raw v = 0;
-            if ((w >> r) & 1ull) { v = stage[rank]; rank++; }
-            if ((uint64_t)(64 * r + l) < rem) store_row<E>(&col[64 * r], v);
+    constexpr uint32_t rows = LineOut<E>::kRows, elems = LineOut<E>::kElems;
+#pragma unroll 1
+    for (uint32_t u = 0; u < 64 / rows; u++) {
+        const uint64_t e0 = (uint64_t)u * elems;
+        if (e0 >= rem) break;
+        raw* col = out.clear() + lane_id();
+        uint32_t sub = rows == 32 ? (uint32_t)(w >> (32 * u)) : (uint32_t)(w >> (rows * u)) & ((1u << (rows & 31)) - 1u);
+        rank = scatter_column<E>(sub, rank, stage, col);
+        const bool end = e0 + elems >= rem;
+        out.flush(end ? (uint32_t)(rem - e0) : elems, last && (end || u + 1 == 64 / rows));
+    }
+}
+
+// Tiles with more values than one wave stages, left by a block's waves for
+// the whole block (block_tiles): up to K per wave; cnt = 0 where there is none.
+template <class E, int K>
+struct DenseTiles {
+    uint64_t w[K];                    // this lane's column word
+    uint32_t pref[K], cnt[K], rem[K]; // its first value, the tile's values, its elements below n
+    const typename E::raw* src[K];    // the tile's values
+    typename E::raw* out[K];          // the tile's elements
+};
+
+// What the waves share of the tile at hand.
+struct TileLds {
+    uint64_t w[64];
+    uint32_t pref[64];
+    uint64_t src, out;
+    uint32_t cnt, rem;
+};
+
+// Each such tile by the four waves together: its values fill the waves'
+// stages as one pool (4 x kChunkVals values: any tile), loaded coalesced with
+// sixteen reads per thread in flight, then each wave assembles and stores a
+// quarter of its rows.  One wave alone had to stage 16 columns at a time and
+// store their elements singly, a quarter of its lanes at work: 256 MiB at 50%
+// sparsity took 376 us in bf16 and 156 us in fp32, now 117 and 109.  Called by
+// every thread of the block.
+template <class E, int K>
+__device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename E::raw* pool, uint4* lines, TileLds* c) {
+    using raw = typename E::raw;
+    static_assert(kWavesPerBlock * kChunkVals == kTileElems && kBlockThreads * 16 == kTileElems, "the pool holds any tile");
+    const uint32_t wave = threadIdx.x >> 6, l = lane_id();
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < K; k++) any = any || d.cnt[k] != 0u;
+    if (!__syncthreads_or(any)) return;
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+#pragma unroll 1
+        for (uint32_t v = 0; v < kWavesPerBlock; v++) {
+            if (wave == v) {
+                c->w[l] = d.w[k];
+                c->pref[l] = d.pref[k];
+                if (l == 0) {
+                    c->src = reinterpret_cast<uint64_t>(d.src[k]);
+                    c->out = reinterpret_cast<uint64_t>(d.out[k]);
+                    c->cnt = d.cnt[k];
+                    c->rem = d.rem[k];
+                }
+            }
+            __syncthreads();
+            const uint32_t cnt = c->cnt, rem = c->rem;
+            const raw* src = reinterpret_cast<const raw*>(c->src);
+            raw* out = reinterpret_cast<raw*>(c->out);
+            const uint64_t w = c->w[l];
+            const uint32_t pref = c->pref[l];
+            if (cnt) {
+                raw x[16];
+#pragma unroll
+                for (uint32_t j = 0; j < 16; j++) {
+                    const uint32_t i = threadIdx.x + kBlockThreads * j;
+                    x[j] = i < cnt ? src[i] : (raw)0;
+                }
+#pragma unroll
+                for (uint32_t j = 0; j < 16; j++) {
+                    const uint32_t i = threadIdx.x + kBlockThreads * j;
+                    if (i < cnt) pool[i] = x[j];
+                }
+            }
+            __syncthreads();           // the pool is filled; c may be written again
+            const uint32_t e0 = 1024u * wave;
+            if (cnt && e0 < rem) {
+                LineOut<E> run;
+                run.start(lines, out + e0);
+                raw* col = run.clear() + l;
+                scatter_column<E>((uint32_t)(w >> (16 * wave)) & 0xFFFFu,
+                                  pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)), pool, col);
+                run.flush(rem - e0 < 1024u ? rem - e0 : 1024u, true);
+            }
         }
     }
 }
 
 // Tiles [t0, tend) of a COO expansion, from entries lo .. lo + cnt of J and
-// V (checked, in index order), a quarter tile (16 rows, kChunkVals elements)
-// at a time: the quarter is zeroed in the wave's LDS buffer, the entries that
-// fall in it are written there, and it is stored with 16-byte stores (element
-// stores when out is not 16-byte aligned).  Entries are held in registers a
-// chunk (kCooChunk) at a time, the first chunk (m entries) already loaded; a
-// quarter takes entries from the next chunks until the held chunk reaches
-// past it.  Every element is written once: zeroing the output first and then
-// storing the values over it wrote the lines twice.  Elements at or past n are
-// not written.
+// V (checked, in index order), a unit (LineOut) at a time: the entries that
+// fall in the unit are written there by index, and it is stored.  Entries
+// are held in registers a chunk (kCooChunk) at a time, the first chunk (m
+// entries) already loaded; a unit takes entries from the next chunks until
+// the held chunk reaches past it.  Every element is written once: zeroing the
+// output first and then storing the values over it wrote the lines twice.
+// Elements at or past n are not written.
 template <class E>
 __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename E::raw* V, uint32_t lo, uint32_t cnt,
                                               uint32_t m, uint32_t (&x)[kCooSlots], typename E::raw (&val)[kCooSlots],
                                               uint64_t t0, uint64_t tend, uint64_t n, typename E::raw* out,
-                                              typename E::raw* buf) {
+                                              uint4* lines) {
     using raw = typename E::raw;
-    constexpr uint32_t per16 = 16 / sizeof(raw);
-    constexpr uint32_t chunks = kChunkVals / per16;           // 16-byte chunks of a quarter
-    static_assert(chunks % 64 == 0, "whole chunks per lane");
+    constexpr uint32_t elems = LineOut<E>::kElems;
     const uint32_t l = lane_id();
-    const bool vec = (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
-    uint4* b4 = reinterpret_cast<uint4*>(buf);
+    LineOut<E> run;
+    run.start(lines, out + t0 * kTileElems);
+    const uint64_t end = tend * kTileElems < n ? tend * kTileElems : n;
     uint32_t c0 = 0;                                          // entries before the held chunk
 #pragma unroll 1
-    for (uint64_t base = t0 * kTileElems; base < tend * kTileElems && base < n; base += kChunkVals) {
-        const uint64_t rem = n - base;
+    for (uint64_t base = t0 * kTileElems; base < end; base += elems) {
         const uint32_t b32 = (uint32_t)base;                  // indices are below 2^32
-#pragma unroll
-        for (uint32_t k = 0; k < chunks / 64; k++) b4[l + 64 * k] = uint4{0, 0, 0, 0};
-        wave_lds_sync();
+        raw* buf = run.clear();
 #pragma unroll 1
         while (true) {
 #pragma unroll
             for (int q = 0; q < kCooSlots; q++) {
                 const uint32_t rel = x[q] - b32;
-                if (l + 64u * q < m && rel < kChunkVals) buf[rel] = val[q];
+                if (l + 64u * q < m && rel < elems) buf[rel] = val[q];
             }
             if (c0 + m >= cnt) break;                         // no entries beyond the held chunk
             uint32_t xl = 0;                                  // index of the held chunk's last entry
 #pragma unroll
             for (int q = 0; q < kCooSlots; q++)
                 if ((uint32_t)q == (m - 1) / 64) xl = x[q];
-            if (lane_bcast(xl, (m - 1) % 64) - b32 >= kChunkVals) break;   // it reaches past this quarter
+            if (lane_bcast(xl, (m - 1) % 64) - b32 >= elems) break;   // it reaches past this unit
             c0 += m;
             m = cnt - c0 < kCooChunk ? cnt - c0 : kCooChunk;
             coo_load_pairs<E>(J, V, lo + c0, m, false, 0, 0, x, val);
         }
-        wave_lds_sync();
-        raw* o = out + base;
-#pragma unroll
-        for (uint32_t k = 0; k < chunks / 64; k++) {
-            const uint32_t c = l + 64 * k;
-            const uint64_t e0 = (uint64_t)c * per16;
-            if (vec && e0 + per16 <= rem) {
-                st_stream(reinterpret_cast<uint4*>(o) + c, b4[c]);
-            } else if (e0 < rem) {
-                const uint32_t k1 = rem - e0 < per16 ? (uint32_t)(rem - e0) : per16;
-                for (uint32_t k = 0; k < k1; k++) st_stream(&o[e0 + k], buf[e0 + k]);
-            }
-        }
-        wave_lds_sync();
+        const uint64_t left = end - base;
+        run.flush(left < elems ? (uint32_t)left : elems, left <= elems);
     }
 }
 
@@ -2513,7 +2678,8 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
 template <class E, int K>
 __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* d, uint32_t fmt, uint64_t nnz,
                                              uint64_t n, uint64_t T, uint64_t t0, typename E::raw* out,
-                                             typename E::raw* stage, WsCtrl* ctrl) {
+                                             typename E::raw* stage, uint4* lines, WsCtrl* ctrl,
+                                             DenseTiles<E, K>& dense) {
     using raw = typename E::raw;
     const uint32_t l = lane_id();
     const uint64_t g_n = n, g_T = T;
@@ -2541,7 +2707,7 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
             cnt = m = 0;
             if (l == 0) set_status(ctrl, SPCCL_ERR_CORRUPT_STREAM);
         }
-        coo_tiles_lds<E>(J, V, lo, cnt, m, x, val, t0, tend, g_n, out, stage);
+        coo_tiles_lds<E>(J, V, lo, cnt, m, x, val, t0, tend, g_n, out, lines);
         return;
     }
     if (fmt != (uint32_t)kFmtPici) {
@@ -2619,42 +2785,34 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
         }
         wave_lds_sync();
     }
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        if (k >= kfit) break;
-        store_from_stage<E>(out + (t0 + k) * kTileElems + l, g_n - (t0 + k) * kTileElems, cw[k], stage,
-                            (cbase[k] - cbase[0]) + cpref[k]);
-    }
-    // the rest one at a time
+    // the tiles in order, each from the stage: the leading ones share it,
+    // every other one is staged on its own once the tile before it is stored
+    LineOut<E> run;
+    bool running = false;
 #pragma unroll
     for (int k = 0; k < K; k++) {
         const uint64_t t = t0 + k;
-        if (k < kfit) continue;
         if (t >= g_T) break;
-        raw* col = out + t * kTileElems + l;
         const uint64_t rem = g_n - t * kTileElems;
         const uint64_t w = cw[k];
         const uint32_t cnt = ccnt[k];
         if (cnt <= kChunkVals) {
-            wave_lds_sync();
-            for (uint32_t i = l; i < cnt; i += 64) stage[i] = A[cbase[k] + i];
-            wave_lds_sync();
-            store_from_stage<E>(col, rem, w, stage, cpref[k]);
-        } else {
-            // dense tile: 16 columns at a time; their values (contiguous in A,
-            // at most 1024) are staged with coalesced loads, then the group's
-            // lanes write their columns
-            const uint32_t myp = cpref[k];
-#pragma unroll 1
-            for (int h = 0; h < 4; h++) {
-                const uint32_t c0 = 16u * h;
-                const uint32_t lo = lane_bcast(myp, c0);
-                const uint32_t hi = h == 3 ? cnt : lane_bcast(myp, c0 + 16);
+            if (k >= kfit) {
                 wave_lds_sync();
-                stage_values<E>(A + cbase[k] + lo, hi - lo, stage);
+                stage_values<E>(A + cbase[k], cnt, stage);
                 wave_lds_sync();
-                if (l >= c0 && l < c0 + 16) store_from_stage<E>(col, rem, w, stage, myp - lo);
             }
+            if (!running) run.start(lines, out + t * kTileElems);
+            const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
+            store_from_stage<E>(run, rem, w, stage, k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], last);
+            running = !last;
+        } else {
+            dense.w[k] = w;                       // left for the block
+            dense.pref[k] = cpref[k];
+            dense.cnt[k] = cnt;
+            dense.rem[k] = (uint32_t)(rem < kTileElems ? rem : kTileElems);
+            dense.src[k] = A + cbase[k];
+            dense.out[k] = out + t * kTileElems;
         }
     }
 }
@@ -2663,7 +2821,9 @@ template <class E, int K>
 __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_part, uint64_t n, uint64_t T,
                                             WsCtrl* ctrl) {
     using raw = typename E::raw;
-    __shared__ __attribute__((aligned(16))) raw stage_all[kWavesPerBlock][kChunkVals];
+    __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
+    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
+    __shared__ TileLds tile;
     __shared__ uint32_t s_ok, s_fmt;
     __shared__ uint64_t s_nnz;
     const uint32_t wave = threadIdx.x >> 6;
@@ -2679,10 +2839,11 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
     __syncthreads();
     if (!s_ok) return;
     const uint64_t t0 = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * K;
-    if (t0 >= T) return;
     raw* out = reinterpret_cast<raw*>(out_part);
     const uint8_t* d = op.hdr ? op.hdr + kHeaderBytes : op.data;
-    expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], ctrl);
+    DenseTiles<E, K> dense{};
+    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], lines_all[wave], ctrl, dense);
+    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
 }
 
 template <class E, int K>
@@ -2871,21 +3032,27 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
     using raw = typename E::raw;
     constexpr uint32_t K = kTilesPerPart / kExpandWavesPerSlice;
     __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
+    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
+    __shared__ TileLds tile;
     const uint32_t wave = threadIdx.x >> 6;
     const uint64_t wq = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
     const uint64_t q = wq / kExpandWavesPerSlice, t0 = K * (wq % kExpandWavesPerSlice);
-    if (q >= num_slices(g.n)) return;
     const uint64_t base = q * kSliceElems;
-    const uint64_t ns = g.n - base < kSliceElems ? g.n - base : kSliceElems;
-    if (t0 >= num_tiles(ns)) return;                      // a short last slice
-    const uint8_t* bm = g.a + q * g.slot;
-    const HeaderView h = check_header(load_header_words(bm), g.slot, ns, E::dtype, -1);
-    if (!h.ok || h.fmt == (uint32_t)kFmtCoo) {           // slices are Pici or dense
-        if (lane_id() == 0) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
-        return;
+    DenseTiles<E, K> dense{};
+    if (q < num_slices(g.n)) {
+        const uint64_t ns = g.n - base < kSliceElems ? g.n - base : kSliceElems;
+        if (t0 < num_tiles(ns)) {                             // else a short last slice
+            const uint8_t* bm = g.a + q * g.slot;
+            const HeaderView h = check_header(load_header_words(bm), g.slot, ns, E::dtype, -1);
+            if (!h.ok || h.fmt == (uint32_t)kFmtCoo) {        // slices are Pici or dense
+                if (lane_id() == 0) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
+            } else {
+                expand_tiles<E, K>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
+                                   reinterpret_cast<raw*>(g.out) + base, stage_all[wave], lines_all[wave], g.ctrl, dense);
+            }
+        }
     }
-    expand_tiles<E, K>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
-                       reinterpret_cast<raw*>(g.out) + base, stage_all[wave], g.ctrl);
+    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
 }
 
 template <class E>
