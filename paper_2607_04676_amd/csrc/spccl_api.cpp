@@ -15,9 +15,7 @@ spccl_status_t launch_to_pici_dt(int dtype, int sa, int sb, const PiciSinkArgs& 
 spccl_status_t launch_to_dense_dt(int dtype, int sa, int sb, const DenseSinkArgs& g, hipStream_t st);
 spccl_status_t launch_to_coo_dt(int dtype, int sa, int sb, const PiciSinkArgs& g, hipStream_t st);
 spccl_status_t launch_gather_dt(int dtype, const GatherArgs& g, int P, hipStream_t st);
-spccl_status_t launch_dense_dense_dt(int dtype, const uint8_t* a_hdr, const uint8_t* a, uint64_t a_cap,
-                                     const uint8_t* b_hdr, const uint8_t* b, uint64_t b_cap, uint8_t* out_hdr,
-                                     uint8_t* out, uint64_t n, WsCtrl* ctrl, hipStream_t st);
+spccl_status_t launch_dense_dense_dt(int dtype, const DenseSinkArgs& g, hipStream_t st);
 spccl_status_t launch_copy_message(const uint8_t* src, uint64_t src_cap, uint8_t* dst, uint64_t dst_cap,
                                    WsCtrl* ctrl, hipStream_t st);
 spccl_status_t launch_fill_zero(void* p, uint64_t bytes, hipStream_t st);
@@ -353,12 +351,12 @@ spccl_status_t spccl_reduce(spccl_operand_t a, spccl_operand_t b, spccl_operand_
     }
     st = check_ws(ws, ws_bytes, kWsFlagsOffset);
     if (st != SPCCL_OK) return st;
-    if (sa.kind == SRC_DENSE && sb.kind == SRC_DENSE)
-        return launch_dense_dense_dt(dtype, sa.dev.hdr, sa.dev.data, sa.dev.cap, sb.dev.hdr, sb.dev.data,
-                                     sb.dev.cap, out_hdr, out_data, n, ctrl, hs);
-    if (n == 0 && !out_hdr) return SPCCL_OK;
-    if ((st = index_coo(sa, 0, n, dtype, ws, ws_bytes, hs)) != SPCCL_OK) return st;
-    if ((st = index_coo(sb, 1, n, dtype, ws, ws_bytes, hs)) != SPCCL_OK) return st;
+    const bool dense = sa.kind == SRC_DENSE && sb.kind == SRC_DENSE;
+    if (!dense) {
+        if (n == 0 && !out_hdr) return SPCCL_OK;
+        if ((st = index_coo(sa, 0, n, dtype, ws, ws_bytes, hs)) != SPCCL_OK) return st;
+        if ((st = index_coo(sb, 1, n, dtype, ws, ws_bytes, hs)) != SPCCL_OK) return st;
+    }
     DenseSinkArgs g{};
     g.a = sa.dev;
     g.b = sb.dev;
@@ -367,6 +365,7 @@ spccl_status_t spccl_reduce(spccl_operand_t a, spccl_operand_t b, spccl_operand_
     g.n = n;
     g.T = num_tiles(n);
     g.ctrl = ctrl;
+    if (dense) return launch_dense_dense_dt(dtype, g, hs);
     return launch_to_dense_dt(dtype, sa.kind, sb.kind, g, hs);
 }
 

@@ -83,6 +83,15 @@ struct DevOperand {
     uint32_t idx_epoch;    // the epoch of this call's index words; a tile whose words carry another searches J
 };
 
+// One rank's send of one step of a ring decided on the device (Sec. IV-C): its
+// sigma0, the tracked sparsity before this send's own count (a Pici send is
+// measured), its count (Pici) and its format.
+struct RingRank {
+    double sigma0, sigma_prev;
+    uint64_t nnz;
+    int32_t fmt, pad;
+};
+
 struct PiciSinkArgs {
     DevOperand a, b;
     uint8_t* out;          // output message base
@@ -94,6 +103,8 @@ struct PiciSinkArgs {
     uint64_t* flags;
     uint8_t* slots;        // two-pass mode: one worst-case slot of compacted values per partition
     uint32_t* idx_slots;   // COO output: one worst-case slot of flat indices per partition
+    uint64_t* nnz_out;     // the output's count once it is known, beside the header (nullptr: not wanted)
+    RingRank* nnz_rows;    // a batch: rank r's count goes to nnz_rows[r].nnz (nullptr: not wanted)
 };
 
 struct DenseSinkArgs {
@@ -137,20 +148,21 @@ struct SlicedArgs {
     double* track;         // per slice: sigma0, sigma_prev (nullptr: decide on the measured sparsity)
     int32_t track_step;    // 0: the first send (sigma0 := measured); 1: a later one (Eq. 7 estimate)
     uint8_t* fmt_out;      // per slice: the format produced (nullptr: not recorded)
+    uint8_t* fwd;          // expand: the stream is also written here, for the next hop (nullptr: not)
 };
 
 // One sliced ring step for up to kMaxBatchRanks virtual ranks in a single
 // launch (grid y = rank): rank r's arguments are base with its own dense or
-// source pointer a[r], its own dense output (out_dense[r], else the strided
-// stream base.out + r out_stride), its threshold, and strided received
-// streams, trackers and format records.
+// source pointer a[r], output out[r] and forwarded stream fwd[r], its
+// threshold, and strided received streams, trackers and format records.
 constexpr int kMaxBatchRanks = 32;
 struct SlicedBatch {
     SlicedArgs base;
     const uint8_t* a[kMaxBatchRanks];
-    uint8_t* out_dense[kMaxBatchRanks];
+    uint8_t* out[kMaxBatchRanks];
+    uint8_t* fwd[kMaxBatchRanks];
     double thresh[kMaxBatchRanks];
-    uint64_t b_stride, out_stride;   // bytes between ranks
+    uint64_t b_stride;               // bytes between ranks
     uint64_t track_stride;           // doubles between ranks
     uint64_t fmt_stride;             // bytes between ranks
 };
@@ -161,52 +173,35 @@ struct SlicedBatch {
 // the status word are the launch's base arguments, shared.  An operand
 // pointer replaces the base operand's (a message keeps its header-to-data
 // offset); a null b leaves the base's b.
-// Per rank of a ring whose formats are decided on the device: its sigma0 and
-// tracked sparsity (Sec. IV-C), and the formats of the message it receives
-// and of the one it sends at the current step.
-struct RingRank {
-    double sigma0, sigma_prev;
-    int32_t in_fmt, out_fmt;
-};
-
 struct RankBatch {
     const uint8_t* a[kMaxBatchRanks];
     const uint8_t* b[kMaxBatchRanks];
     uint8_t* out[kMaxBatchRanks];
     uint8_t* flags[kMaxBatchRanks];     // the rank's look-back words (zeroed once per collective)
     uint8_t* slots[kMaxBatchRanks];     // the rank's value slots (two-pass Pici sink)
-    // With gate set, a rank takes part only if its decided formats match
-    // gate_in / gate_out (-1: any); rank[j] indexes gate for batch entry j.
-    const RingRank* gate;
-    int32_t gate_in, gate_out;
-    int32_t rank[kMaxBatchRanks];
+    const RingRank* gate;               // the place pass: only ranks whose send in this row is Pici (nullptr: all)
+    int32_t rank[kMaxBatchRanks];       // the rank of each entry
 };
 
-// The decisions of one canonical ring step on the device (k_ring_decide):
-// rank r's last send is the message at slots0 + r * slot_bytes.
-enum RingDecide {
-    kDecideFirst = 0,     // after the first compression: sigma0, the first send's format
-    kDecideStep = 1,      // before ring step `step`: the previous step's trace, this step's formats
-    kDecideGather = 2,    // all-reduce transition, before encoding: the gather's formats
-    kDecideGatherSizes = 3,  // after the transition's encoding: its sizes in the trace
-    kDecideAllGather = 4  // a standalone all-gather's sends (every part Pici): their trace
-};
+// The launches of a device-decided ring.
+enum RingLaunch { kRingFirst = 0, kRingStep = 1, kRingGather = 2 };
 
+// The state of a device-decided ring: P ranks a row, one row per send (step 0
+// .. P - 2 of the reduce-scatter, then the all-gather's at row P - 1).
 struct RingArgs {
-    RingRank* rr;             // P entries
-    void* trace;              // spccl_trace_t[P * (P - 1) + P] in device memory
-    const uint8_t* slots0;
+    RingRank* rows;
     uint64_t slot_bytes;
     uint64_t m;               // elements per message
-    int32_t P, step, mode, dtype;
+    int32_t P, step;
+    int32_t last;             // the step that reduces into the output
     double intra, inter, ag;  // the policy's thresholds
     int32_t ranks_per_node, adaptive;
 };
 
+__host__ __device__ inline RingRank* ring_row(const RingArgs& a, int step) { return a.rows + (uint64_t)step * a.P; }
+
 __host__ __device__ inline bool rank_skipped(const RankBatch& rb, uint32_t j) {
-    if (!rb.gate) return false;
-    const RingRank& q = rb.gate[rb.rank[j]];
-    return (rb.gate_in >= 0 && q.in_fmt != rb.gate_in) || (rb.gate_out >= 0 && q.out_fmt != rb.gate_out);
+    return rb.gate && rb.gate[rb.rank[j]].fmt != kFmtPici;
 }
 
 __host__ __device__ inline DevOperand rebase(DevOperand o, const uint8_t* p) {
@@ -225,18 +220,7 @@ __host__ __device__ inline PiciSinkArgs rank_sink(PiciSinkArgs g, const RankBatc
     g.out = rb.out[r];
     g.flags = reinterpret_cast<uint64_t*>(rb.flags[r]);
     g.slots = rb.slots[r];
-    return g;
-}
-
-__host__ __device__ inline DenseSinkArgs rank_dense(DenseSinkArgs g, const RankBatch& rb, uint32_t r) {
-    g.a = rebase(g.a, rb.a[r]);
-    if (rb.b[r]) g.b = rebase(g.b, rb.b[r]);
-    if (g.out_hdr) {
-        g.out_hdr = rb.out[r];
-        g.out = rb.out[r] + kHeaderBytes;
-    } else {
-        g.out = rb.out[r];
-    }
+    if (g.nnz_rows) g.nnz_out = &g.nnz_rows[rb.rank[r]].nnz;
     return g;
 }
 
@@ -244,7 +228,8 @@ __host__ __device__ inline SlicedArgs batch_rank(const SlicedBatch& b, uint32_t 
     SlicedArgs g = b.base;
     g.a = b.a[r];
     if (g.b) g.b = b.base.b + r * b.b_stride;
-    g.out = b.out_dense[r] ? b.out_dense[r] : b.base.out + r * b.out_stride;
+    g.out = b.out[r];
+    g.fwd = b.fwd[r];
     g.thresh = b.thresh[r];
     if (g.track) g.track = b.base.track + r * b.track_stride;
     if (g.fmt_out) g.fmt_out = b.base.fmt_out + r * b.fmt_stride;

@@ -153,6 +153,14 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) {
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(p));
 }
 
+// 16 bytes from any element address (unaligned vector loads).
+template <bool NT>
+__device__ __forceinline__ u32x4 ld_vec(const uint8_t* p) {
+    typedef u32x4 __attribute__((aligned(2))) u32x4u;
+    if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4u*>(p));
+    else return *reinterpret_cast<const u32x4u*>(p);
+}
+
 __device__ __forceinline__ void set_status(WsCtrl* ctrl, uint32_t code) {
     atomicCAS(&ctrl->status, 0u, code);
 }
@@ -1229,16 +1237,24 @@ __device__ uint32_t chunk_lookback(uint64_t* flags, uint32_t nparts, uint32_t p,
 // aggregate, writes B and the tile offsets relative to the partition, and
 // parks its compacted values in its own worst-case slot of the workspace,
 // never waiting on another block; k_place then moves each slot into place.
+// LDS of a sink block (shared by the paths of a kernel that has several).
+template <class E>
+struct SinkLds {
+    typename E::raw stage[kWavesPerBlock][E::cap];
+    typename E::raw spare[kWavesPerBlock][64];            // compact_rows' per-lane slots
+    uint32_t cnt[kWavesPerBlock];
+    uint32_t prefix;
+};
+
 template <class E, int SA, int SB, bool Deferred>
-__device__ __forceinline__ void to_pici_body(const PiciSinkArgs& g) {
+__device__ __forceinline__ void to_pici_body(const PiciSinkArgs& g, SinkLds<E>& lds) {
     using raw = typename E::raw;
-    __shared__ raw stage_all[kWavesPerBlock][E::cap];
-    __shared__ raw spare_all[kWavesPerBlock][64];         // compact_rows' per-lane slots
-    __shared__ uint32_t s_cnt[kWavesPerBlock];
-    __shared__ uint32_t s_prefix;
+    auto& spare_all = lds.spare;
+    auto& s_cnt = lds.cnt;
+    auto& s_prefix = lds.prefix;
 
     const uint32_t wave = threadIdx.x >> 6, l = lane_id();
-    raw* stage = stage_all[wave];
+    raw* stage = lds.stage[wave];
     // Partition = block index.  Work-groups start in index order on each XCD,
     // so the lowest unfinished partition is always resident and every wait
     // below ends (the spin limit bounds it regardless).
@@ -1366,6 +1382,7 @@ __device__ __forceinline__ void to_pici_body(const PiciSinkArgs& g) {
         I[g.T] = (uint32_t)nnz;
         for (uint64_t b = oI + 4 * (g.T + 1); b < oA; b += 4) *reinterpret_cast<uint32_t*>(g.out + b) = 0u;
         write_header(g.out, kFmtPici, E::dtype, g.n, nnz, oI, oA, oA + nnz * sizeof(raw));
+        if (g.nnz_out) *g.nnz_out = nnz;
     }
 }
 
@@ -1377,19 +1394,19 @@ constexpr int sink_waves(int sb, bool deferred) { return (sb == SRC_NONE && defe
 
 template <class E, int SA, int SB, bool Deferred>
 __global__ void __launch_bounds__(kBlockThreads, sink_waves(SB, Deferred)) k_to_pici(PiciSinkArgs g) {
-    to_pici_body<E, SA, SB, Deferred>(g);
+    __shared__ SinkLds<E> lds;
+    to_pici_body<E, SA, SB, Deferred>(g, lds);
 }
 
-// One ring step's Pici outputs for a batch of ranks (grid y), in one launch
-// or as the count pass.  Work-groups start in order of the flattened block
-// index, so a rank's blocks start after those of lower ranks, and a block
-// waits only for lower partitions of its own rank.
-template <class E, int SA, int SB, bool Deferred>
-__global__ void __launch_bounds__(kBlockThreads, sink_waves(SB, Deferred)) k_to_pici_rb(PiciSinkArgs g, RankBatch rb) {
-    if (rank_skipped(rb, blockIdx.y)) return;
-    to_pici_body<E, SA, SB, Deferred>(rank_sink(g, rb, blockIdx.y));
+// The compressions of a batch of ranks (grid y), in one launch or as the
+// count pass.  Work-groups start in order of the flattened block index, so a
+// rank's blocks start after those of lower ranks, and a block waits only for
+// lower partitions of its own rank.
+template <class E, bool Deferred>
+__global__ void __launch_bounds__(kBlockThreads, sink_waves(SRC_NONE, Deferred)) k_compress_rb(PiciSinkArgs g, RankBatch rb) {
+    __shared__ SinkLds<E> lds;
+    to_pici_body<E, SRC_DENSE, SRC_NONE, Deferred>(rank_sink(g, rb, blockIdx.y), lds);
 }
-
 
 // ---------------------------------------------------------------------------
 // Pici (+) Pici -> Pici with work proportional to the nonzeros.
@@ -1641,6 +1658,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_pp_tile(PiciSinkArgs g) {
         I[g.T] = (uint32_t)nnz;
         for (uint64_t b = oI + 4 * (g.T + 1); b < oA; b += 4) *reinterpret_cast<uint32_t*>(g.out + b) = 0u;
         write_header(g.out, kFmtPici, E::dtype, g.n, nnz, oI, oA, oA + nnz * sizeof(raw));
+        if (g.nnz_out) *g.nnz_out = nnz;
     }
 }
 
@@ -1902,6 +1920,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_pp_part(PiciSinkArgs g) {
         I[g.T] = (uint32_t)nnz;
         for (uint64_t b = oI + 4 * (g.T + 1); b < oA; b += 4) *reinterpret_cast<uint32_t*>(g.out + b) = 0u;
         write_header(g.out, kFmtPici, E::dtype, g.n, nnz, oI, oA, oA + nnz * sizeof(raw));
+        if (g.nnz_out) *g.nnz_out = nnz;
     }
 }
 
@@ -2068,6 +2087,7 @@ __device__ __forceinline__ void place_body(const PiciSinkArgs& g) {
         I[g.T] = (uint32_t)nnz;
         for (uint64_t b = oI + 4 * (g.T + 1); b < oA; b += 4) *reinterpret_cast<uint32_t*>(g.out + b) = 0u;
         write_header(g.out, kFmtPici, E::dtype, g.n, nnz, oI, oA, oA + nnz * sizeof(raw));
+        if (g.nnz_out) *g.nnz_out = nnz;
     }
 }
 
@@ -2340,10 +2360,9 @@ __device__ __forceinline__ void store_tile(uint8_t* out, uint64_t t, uint64_t n,
 }
 
 template <class E, int SA, int SB>
-__device__ __forceinline__ void to_dense_body(const DenseSinkArgs& g) {
+__device__ __forceinline__ void to_dense_body(const DenseSinkArgs& g, typename E::raw (&stage_all)[kWavesPerBlock][E::cap]) {
     using raw = typename E::raw;
     constexpr bool coo = SA == SRC_COO || SB == SRC_COO;
-    __shared__ raw stage_all[kWavesPerBlock][E::cap];
     __shared__ CooLds coo_all[coo ? kWavesPerBlock : 1];
     const uint32_t wave = threadIdx.x >> 6;
     const uint64_t t = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
@@ -2363,13 +2382,8 @@ __device__ __forceinline__ void to_dense_body(const DenseSinkArgs& g) {
 
 template <class E, int SA, int SB>
 __global__ void __launch_bounds__(kBlockThreads) k_to_dense(DenseSinkArgs g) {
-    to_dense_body<E, SA, SB>(g);
-}
-
-template <class E, int SA, int SB>
-__global__ void __launch_bounds__(kBlockThreads) k_to_dense_rb(DenseSinkArgs g, RankBatch rb) {
-    if (rank_skipped(rb, blockIdx.y)) return;
-    to_dense_body<E, SA, SB>(rank_dense(g, rb, blockIdx.y));
+    __shared__ typename E::raw stage_all[kWavesPerBlock][E::cap];
+    to_dense_body<E, SA, SB>(g, stage_all);
 }
 
 // Expansion of P parts (all-gather receive side and decompress): the format
@@ -2386,27 +2400,43 @@ __global__ void __launch_bounds__(kBlockThreads) k_to_dense_rb(DenseSinkArgs g, 
 // is paid once per K tiles.  Tiles that do not fit are expanded one at a
 // time (stage their values, then write), and tiles holding more than
 // kChunkVals values by the whole block (block_tiles).
-// Rows [r0, r0 + 16) of dense tile t (bounded buffer loads, zero past n).
+// `cnt` elements from src to dst and, if fwd is given, to fwd as well, by one
+// wave: 16 bytes per lane, eight loads in flight before their stores, vectors
+// aligned on the destination.  A forwarded run whose two destinations are
+// both aligned is read once.
 template <class E>
-__device__ __forceinline__ void fetch_dense_rows16(const uint8_t* base, uint64_t t, uint64_t n, int r0,
-                                                   uint32_t (&v)[16]) {
+__device__ __forceinline__ void copy_wave(const typename E::raw* src, typename E::raw* dst, typename E::raw* fwd,
+                                          uint64_t cnt) {
     using raw = typename E::raw;
-    constexpr uint32_t rowb = 64 * sizeof(raw);
-    t = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(t >> 32)) << 32) |
-        __builtin_amdgcn_readfirstlane((uint32_t)t);
-    const uint64_t start = t * kTileElems;
-    const uint64_t rem = start < n ? n - start : 0;
-    const uint32_t bytes = (uint32_t)((rem < kTileElems ? rem : kTileElems) * sizeof(raw));
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint8_t*>(base) + (rem ? start : 0) * sizeof(raw), (short)0, (int)bytes, kBufferWord3);
-    const uint32_t lo = lane_id() * (uint32_t)sizeof(raw);
-    const int soff = (int)(rowb * (uint32_t)r0);
+    constexpr uint32_t s = sizeof(raw);
+    const uint32_t l = lane_id();
+    const uint64_t skew = (reinterpret_cast<uintptr_t>(dst) & 15u) / s;
+    uint64_t head = skew ? 16 / s - skew : 0;
+    if (head > cnt) head = cnt;
+    const uint64_t nv = (cnt - head) * s / 16, v1 = head + nv * (16 / s);
+    const uint8_t* s8 = reinterpret_cast<const uint8_t*>(src + head);
+    u32x4* d4 = reinterpret_cast<u32x4*>(dst + head);
+    u32x4* f4 = reinterpret_cast<u32x4*>(fwd + (fwd ? head : 0));
+#pragma unroll 1
+    for (uint64_t i0 = l; i0 < nv; i0 += 64 * 8) {
+        u32x4 x[8];
 #pragma unroll
-    for (int q = 0; q < 16; q++) {
-        if constexpr (sizeof(raw) == 4)
-            v[q] = __builtin_amdgcn_raw_buffer_load_b32(rs, lo + rowb * q, soff, kStreamLoad);
-        else
-            v[q] = __builtin_amdgcn_raw_buffer_load_b16(rs, lo + rowb * q, soff, kStreamLoad);
+        for (int u = 0; u < 8; u++) x[u] = i0 + 64u * u < nv ? ld_vec<true>(s8 + 16 * (i0 + 64u * u)) : u32x4{0, 0, 0, 0};
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (i0 + 64u * u < nv) __builtin_nontemporal_store(x[u], &d4[i0 + 64u * u]);
+        if (fwd) {
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (i0 + 64u * u < nv) __builtin_nontemporal_store(x[u], &f4[i0 + 64u * u]);
+        }
+    }
+    const uint64_t rest = head + (cnt - v1);
+    if (l < rest) {
+        const uint64_t e = l < head ? l : v1 + (l - head);
+        const raw x = src[e];
+        st_stream(&dst[e], x);
+        if (fwd) st_stream(&fwd[e], x);
     }
 }
 
@@ -2552,13 +2582,14 @@ struct DenseTiles {
     uint32_t pref[K], cnt[K], rem[K]; // its first value, the tile's values, its elements below n
     const typename E::raw* src[K];    // the tile's values
     typename E::raw* out[K];          // the tile's elements
+    typename E::raw* fwd[K];          // where its values are forwarded to (nullptr: not)
 };
 
 // What the waves share of the tile at hand.
 struct TileLds {
     uint64_t w[64];
     uint32_t pref[64];
-    uint64_t src, out;
+    uint64_t src, out, fwd;
     uint32_t cnt, rem;
 };
 
@@ -2588,6 +2619,7 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename 
                 if (l == 0) {
                     c->src = reinterpret_cast<uint64_t>(d.src[k]);
                     c->out = reinterpret_cast<uint64_t>(d.out[k]);
+                    c->fwd = reinterpret_cast<uint64_t>(d.fwd[k]);
                     c->cnt = d.cnt[k];
                     c->rem = d.rem[k];
                 }
@@ -2596,6 +2628,7 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename 
             const uint32_t cnt = c->cnt, rem = c->rem;
             const raw* src = reinterpret_cast<const raw*>(c->src);
             raw* out = reinterpret_cast<raw*>(c->out);
+            raw* fwd = reinterpret_cast<raw*>(c->fwd);
             const uint64_t w = c->w[l];
             const uint32_t pref = c->pref[l];
             if (cnt) {
@@ -2609,6 +2642,7 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename 
                 for (uint32_t j = 0; j < 16; j++) {
                     const uint32_t i = threadIdx.x + kBlockThreads * j;
                     if (i < cnt) pool[i] = x[j];
+                    if (fwd && i < cnt) fwd[i] = x[j];
                 }
             }
             __syncthreads();           // the pool is filled; c may be written again
@@ -2673,13 +2707,16 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
 
 // Tiles [t0, t0 + K) of one checked message (format fmt, nnz nonzeros, n
 // elements, T tiles; d = its dense values for a dense message, msg = the
-// message for a Pici one) expanded into out[0 .. n).  One wave; all reads
-// before the first store (see k_gather).
+// message for a Pici one) expanded into out[0 .. n) and, if fwd is given,
+// forwarded: the message itself (Pici or dense) is also written there, each
+// wave its tiles' parts, while it is at hand (an all-gather hop used to copy
+// the message first and then read the copy).  One wave; all reads before the
+// first store (see k_gather).
 template <class E, int K>
 __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* d, uint32_t fmt, uint64_t nnz,
                                              uint64_t n, uint64_t T, uint64_t t0, typename E::raw* out,
                                              typename E::raw* stage, uint4* lines, WsCtrl* ctrl,
-                                             DenseTiles<E, K>& dense) {
+                                             DenseTiles<E, K>& dense, uint8_t* fwd) {
     using raw = typename E::raw;
     const uint32_t l = lane_id();
     const uint64_t g_n = n, g_T = T;
@@ -2711,50 +2748,19 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
         return;
     }
     if (fmt != (uint32_t)kFmtPici) {
-        // a dense message: a plain copy of the wave's tiles, 16 bytes per
-        // lane with eight loads in flight before their stores when source
-        // and destination are 16-byte aligned (4.7 -> 6 TB/s for the dense
-        // parts of an all-gather hop); else 16 rows at a time
-        if (((reinterpret_cast<uintptr_t>(d) | reinterpret_cast<uintptr_t>(out)) & 15u) == 0) {
-            const uint64_t e_lo = t0 * kTileElems;
-            const uint64_t e_hi = (t0 + K) * kTileElems < g_n ? (t0 + K) * kTileElems : g_n;
-            const uint64_t nv = (e_hi - e_lo) * sizeof(raw) / 16;
-            const u32x4* s4 = reinterpret_cast<const u32x4*>(reinterpret_cast<const raw*>(d) + e_lo);
-            u32x4* d4 = reinterpret_cast<u32x4*>(out + e_lo);
+        const uint64_t e_lo = t0 * kTileElems;
+        const uint64_t e_hi = (t0 + K) * kTileElems < g_n ? (t0 + K) * kTileElems : g_n;
+        raw* f = fwd ? reinterpret_cast<raw*>(fwd + kHeaderBytes) + e_lo : nullptr;
+        const bool once = f && ((reinterpret_cast<uintptr_t>(out + e_lo) | reinterpret_cast<uintptr_t>(f)) & 15u) == 0;
 #pragma unroll 1
-            for (uint64_t i0 = l; i0 < nv; i0 += 64 * 8) {
-                u32x4 x[8];
-#pragma unroll
-                for (int u = 0; u < 8; u++)
-                    x[u] = i0 + 64u * u < nv ? __builtin_nontemporal_load(&s4[i0 + 64u * u]) : u32x4{0, 0, 0, 0};
-#pragma unroll
-                for (int u = 0; u < 8; u++)
-                    if (i0 + 64u * u < nv) __builtin_nontemporal_store(x[u], &d4[i0 + 64u * u]);
-            }
-            const raw* se = reinterpret_cast<const raw*>(d);
-            for (uint64_t e = e_lo + nv * 16 / sizeof(raw) + l; e < e_hi; e += 64) out[e] = se[e];
-            return;
-        }
-#pragma unroll 1
-        for (int k = 0; k < K; k++) {
-            const uint64_t t = t0 + k;
-            if (t >= g_T) break;
-            raw* col = out + t * kTileElems + l;
-            const uint64_t rem = g_n - t * kTileElems;
-#pragma unroll 1
-            for (int h = 0; h < 4; h++) {
-                uint32_t v[16];
-                fetch_dense_rows16<E>(d, t, g_n, 16 * h, v);
-#pragma unroll
-                for (int q = 0; q < 16; q++) {
-                    const int r = 16 * h + q;
-                    if ((uint64_t)(64 * r + l) < rem) st_stream(&col[64 * r], (raw)v[q]);
-                }
-            }
-        }
+        for (int pass = f && !once ? 0 : 1; pass < 2; pass++)
+            copy_wave<E>(reinterpret_cast<const raw*>(d) + e_lo, pass ? out + e_lo : f, once ? f : nullptr, e_hi - e_lo);
+        if (fwd && t0 == 0 && l == 0)
+            write_header(fwd, kFmtDense, E::dtype, g_n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(g_n, E::dtype));
         return;
     }
     const raw* A = reinterpret_cast<const raw*>(msg + off_A(g_n));
+    raw* fA = reinterpret_cast<raw*>(fwd + (fwd ? off_A(g_n) : 0));
     PiciMeta m[K];
 #pragma unroll
     for (int k = 0; k < K; k++)
@@ -2784,6 +2790,29 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
             if (i < chunk) stage[i] = (raw)x[j];
         }
         wave_lds_sync();
+        if (fwd) {
+#pragma unroll
+            for (int j = 0; j < kChunkSlots; j++) {
+                const uint32_t i = l + 64 * j;
+                if (i < chunk) fA[cbase[0] + i] = (raw)x[j];
+            }
+        }
+    }
+    if (fwd) {
+        uint64_t* fB = reinterpret_cast<uint64_t*>(fwd + kHeaderBytes);
+        uint32_t* fI = reinterpret_cast<uint32_t*>(fwd + off_I(g_n));
+#pragma unroll
+        for (int k = 0; k < K; k++) {
+            if (t0 + k >= g_T) break;
+            fB[(t0 + k) * 64 + l] = m[k].w;
+            if (l == 0) fI[t0 + k] = m[k].base;
+            if (l == 0 && t0 + k + 1 == g_T) {
+                fI[g_T] = m[k].next;
+                for (uint64_t p = off_I(g_n) + 4 * (g_T + 1); p < off_A(g_n); p += 4) *reinterpret_cast<uint32_t*>(fwd + p) = 0u;
+            }
+        }
+        if (t0 == 0 && l == 0)
+            write_header(fwd, kFmtPici, E::dtype, g_n, nnz, off_I(g_n), off_A(g_n), off_A(g_n) + nnz * sizeof(raw));
     }
     // the tiles in order, each from the stage: the leading ones share it,
     // every other one is staged on its own once the tile before it is stored
@@ -2801,6 +2830,8 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
                 wave_lds_sync();
                 stage_values<E>(A + cbase[k], cnt, stage);
                 wave_lds_sync();
+                if (fwd)
+                    for (uint32_t i = l; i < cnt; i += 64) fA[cbase[k] + i] = stage[i];
             }
             if (!running) run.start(lines, out + t * kTileElems);
             const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
@@ -2813,13 +2844,14 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
             dense.rem[k] = (uint32_t)(rem < kTileElems ? rem : kTileElems);
             dense.src[k] = A + cbase[k];
             dense.out[k] = out + t * kTileElems;
+            dense.fwd[k] = fwd ? fA + cbase[k] : nullptr;
         }
     }
 }
 
 template <class E, int K>
 __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_part, uint64_t n, uint64_t T,
-                                            WsCtrl* ctrl) {
+                                            WsCtrl* ctrl, uint8_t* fwd) {
     using raw = typename E::raw;
     __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
     __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
@@ -2842,21 +2874,22 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
     raw* out = reinterpret_cast<raw*>(out_part);
     const uint8_t* d = op.hdr ? op.hdr + kHeaderBytes : op.data;
     DenseTiles<E, K> dense{};
-    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], lines_all[wave], ctrl, dense);
+    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], lines_all[wave], ctrl, dense, fwd);
     block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
 }
 
 template <class E, int K>
 __global__ void __launch_bounds__(kBlockThreads) k_gather(GatherArgs g) {
     gather_body<E, K>(g.part[blockIdx.y], g.out + (uint64_t)blockIdx.y * g.n * sizeof(typename E::raw), g.n, g.T,
-                      g.ctrl);
+                      g.ctrl, nullptr);
 }
 
-// One all-gather hop for a batch of ranks (grid y): each rank expands its
-// received message (part rebased to rb.a) into rb.out.
+// One all-gather hop for a batch of ranks (grid y): each rank expands the
+// message it receives (part rebased to rb.a) into rb.out and writes it to
+// rb.slots, its own buffer, for the next hop (nullptr: not).
 template <class E, int K>
 __global__ void __launch_bounds__(kBlockThreads) k_gather_rb(DevOperand part, uint64_t n, WsCtrl* ctrl, RankBatch rb) {
-    gather_body<E, K>(rebase(part, rb.a[blockIdx.y]), rb.out[blockIdx.y], n, num_tiles(n), ctrl);
+    gather_body<E, K>(rebase(part, rb.a[blockIdx.y]), rb.out[blockIdx.y], n, num_tiles(n), ctrl, rb.slots[blockIdx.y]);
 }
 
 // ---------------------------------------------------------------------------
@@ -3048,7 +3081,8 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
                 if (lane_id() == 0) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
             } else {
                 expand_tiles<E, K>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
-                                   reinterpret_cast<raw*>(g.out) + base, stage_all[wave], lines_all[wave], g.ctrl, dense);
+                                   reinterpret_cast<raw*>(g.out) + base, stage_all[wave], lines_all[wave], g.ctrl, dense,
+                                   g.fwd ? g.fwd + q * g.slot : nullptr);
             }
         }
     }
@@ -3101,20 +3135,145 @@ __global__ void __launch_bounds__(kBlockThreads) k_copy_sliced(SlicedArgs g, uin
     copy_slice(g, nslices);
 }
 
-// The sends of one ring step for a batch of virtual ranks (blockIdx.y).
-__global__ void __launch_bounds__(kBlockThreads) k_copy_sliced_batch(SlicedBatch b, uint64_t nslices) {
-    copy_slice(batch_rank(b, blockIdx.y), nslices);
+// ---------------------------------------------------------------------------
+// dense streams: dense (+) dense -> dense (the dense ring step), and plain
+// copies (dense messages)
+//
+// A block takes one contiguous range, 16 bytes per lane and four vectors in
+// flight per operand, and every range has a block of its own: blocks start in
+// index order, so the device works through memory as a front.  A grid capped
+// at 8192 blocks striding over the array lets the blocks drift apart and ran
+// at 4.8 TB/s (8 x 128 MiB sums) where this form runs at 6.1; a probe of plain
+// writes 4.0 against 6.7.  Vectors are aligned on the output; the operands
+// may start at any element and are then read with unaligned vector loads.
+// Beyond what the Infinity Cache holds, operands are read non-temporally
+// (256 MiB sums 137.9 -> 124.1 us); below, ordinary loads find what the
+// previous call left there.
+constexpr uint64_t kStreamChunk = 16384;           // bytes of output per block
+constexpr uint64_t kCacheBytes = 256ull << 20;     // the Infinity Cache
+
+__device__ __forceinline__ u32x4 oplus_vec(F32, u32x4 x, u32x4 y) {
+    u32x4 z;
+#pragma unroll
+    for (int k = 0; k < 4; k++) z[k] = oplus(F32{}, x[k], y[k]);
+    return z;
+}
+__device__ __forceinline__ u32x4 oplus_vec(BF16, u32x4 x, u32x4 y) {
+    u32x4 z;
+#pragma unroll
+    for (int k = 0; k < 4; k++)
+        z[k] = oplus(BF16{}, x[k] & 0xFFFFu, y[k] & 0xFFFFu) | (oplus(BF16{}, x[k] >> 16, y[k] >> 16) << 16);
+    return z;
+}
+
+// out[e0 .. e1) = a (+) b (Two) or a, by the whole block.
+template <class E, bool Two, bool NT>
+__device__ __forceinline__ void stream_range(const uint8_t* a, const uint8_t* b, uint8_t* out, uint64_t e0, uint64_t e1) {
+    using raw = typename E::raw;
+    constexpr uint32_t s = sizeof(raw), U = 4;
+    const raw* ae = reinterpret_cast<const raw*>(a);
+    const raw* be = reinterpret_cast<const raw*>(b);
+    raw* oe = reinterpret_cast<raw*>(out);
+    const uint64_t skew = (reinterpret_cast<uintptr_t>(oe + e0) & 15u) / s;
+    uint64_t v0 = e0 + (skew ? 16 / s - skew : 0);           // first element of a whole vector
+    if (v0 > e1) v0 = e1;
+    const uint64_t nv = (e1 - v0) * s / 16, v1 = v0 + nv * (16 / s);
+    const uint8_t* av = a + v0 * s;
+    const uint8_t* bv = b + v0 * s;
+    u32x4* ov = reinterpret_cast<u32x4*>(oe + v0);
+#pragma unroll 1
+    for (uint64_t i0 = threadIdx.x; i0 < nv; i0 += U * kBlockThreads) {
+        if (i0 - threadIdx.x + U * kBlockThreads <= nv) {
+            u32x4 x[U], y[U];
+#pragma unroll
+            for (uint32_t u = 0; u < U; u++) {
+                x[u] = ld_vec<NT>(av + 16 * (i0 + u * kBlockThreads));
+                if constexpr (Two) y[u] = ld_vec<NT>(bv + 16 * (i0 + u * kBlockThreads));
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < U; u++)
+                __builtin_nontemporal_store(Two ? oplus_vec(E{}, x[u], y[u]) : x[u], &ov[i0 + u * kBlockThreads]);
+        } else {
+            for (uint64_t i = i0; i < nv; i += kBlockThreads) {
+                const u32x4 x = ld_vec<NT>(av + 16 * i);
+                __builtin_nontemporal_store(Two ? oplus_vec(E{}, x, ld_vec<NT>(bv + 16 * i)) : x, &ov[i]);
+            }
+        }
+    }
+    // the elements before and after the whole vectors
+    const uint64_t head = v0 - e0, rest = head + (e1 - v1);
+    if (threadIdx.x < rest) {
+        const uint64_t e = threadIdx.x < head ? e0 + threadIdx.x : v1 + (threadIdx.x - head);
+        if constexpr (Two) st_stream(&oe[e], (raw)oplus(E{}, ae[e], be[e]));
+        else st_stream(&oe[e], ae[e]);
+    }
+}
+
+// Range `part` (elems elements) of a (+) b of n elements; the headers of
+// message operands are checked by every block, the output's written by one.
+template <class E, bool NT>
+__device__ __forceinline__ void dense_dense_body(const DenseSinkArgs& g, uint32_t part, uint64_t elems) {
+    bool ok = true;                       // the same in every thread of the grid
+    if (g.a.hdr) ok = read_header(g.a.hdr, g.a.cap, g.n, E::dtype, kFmtDense).ok;
+    if (g.b.hdr) ok = ok && read_header(g.b.hdr, g.b.cap, g.n, E::dtype, kFmtDense).ok;
+    if (part == 0 && threadIdx.x == 0) {
+        if (!ok) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
+        else if (g.out_hdr)
+            write_header(g.out_hdr, kFmtDense, E::dtype, g.n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(g.n, E::dtype));
+    }
+    if (!ok) return;
+    const uint64_t e0 = (uint64_t)part * elems;
+    if (e0 < g.n) stream_range<E, true, NT>(g.a.data, g.b.data, g.out, e0, g.n - e0 < elems ? g.n : e0 + elems);
+}
+
+template <class E, bool NT>
+__global__ void __launch_bounds__(kBlockThreads) k_dense_dense(DenseSinkArgs g) {
+    dense_dense_body<E, NT>(g, blockIdx.x, kStreamChunk / sizeof(typename E::raw));
+}
+
+// Range `part` of src[0 .. n) into the dense message at out.
+template <class E, bool NT>
+__device__ __forceinline__ void encode_dense_body(const uint8_t* src, uint8_t* out, uint64_t n, uint32_t part,
+                                                  uint64_t elems) {
+    if (part == 0 && threadIdx.x == 0)
+        write_header(out, kFmtDense, E::dtype, n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(n, E::dtype));
+    const uint64_t e0 = (uint64_t)part * elems;
+    if (e0 < n) stream_range<E, false, NT>(src, src, out + kHeaderBytes, e0, n - e0 < elems ? n : e0 + elems);
+}
+
+template <class E, bool NT>
+__global__ void __launch_bounds__(kBlockThreads) k_encode_dense(const uint8_t* src, uint8_t* out, uint64_t n) {
+    encode_dense_body<E, NT>(src, out, n, blockIdx.x, kStreamChunk / sizeof(typename E::raw));
+}
+
+// Plain copies of n elements for a batch of ranks (grid y): rb.a -> rb.out.
+template <class E, bool NT>
+__global__ void __launch_bounds__(kBlockThreads) k_copy_rb(uint64_t n, RankBatch rb) {
+    const uint64_t elems = kStreamChunk / sizeof(typename E::raw), e0 = (uint64_t)blockIdx.x * elems;
+    if (e0 < n)
+        stream_range<E, false, NT>(rb.a[blockIdx.y], rb.a[blockIdx.y], rb.out[blockIdx.y], e0,
+                                   n - e0 < elems ? n : e0 + elems);
 }
 
 // ---------------------------------------------------------------------------
-// Format decisions of the canonical ring on the device (Sec. IV-C), one
-// thread per rank, between the launches of a ring step: the same rule, in
-// the same IEEE double arithmetic, as the host's.  Sparsity = (m - nnz) / m;
-// a send is dense iff its sparsity (first send) or the estimate sigma_prev *
-// sigma0 (Eq. 7, later sends) is <= the link's threshold; a dense send tracks
-// the estimate, a Pici one its measured sparsity.  Each rank's trace entry
-// is written once its values are known: a Pici send's size and count by the
-// next decision, when its header is in.
+// The canonical ring's steps (Sec. IV-B, IV-C), one launch each for all ranks
+// (grid y), decided by the blocks themselves.  Row s of the state (ring_row)
+// holds every rank's send of step s; a step reads the row before its own:
+// rank r's tracked sparsity and last count give its decision, rank r-1's
+// format says what it receives.  Each block works it out alone (a few double
+// operations on one cache line), in the same IEEE arithmetic as the host's
+// rule: sparsity = (m - nnz) / m; a send is dense iff its sparsity (first
+// send) or the estimate sigma_prev * sigma0 (Eq. 7, later sends) is <= the
+// link's threshold; a dense send tracks the estimate, a Pici one its measured
+// sparsity.  One thread per rank writes the step's row; a Pici sink adds its
+// count.  A step used to be six launches (decision, send, and one sink per
+// pair of formats, three of them with nothing to do, 4-5 us each): the P = 8
+// reduce-scatter of 33,554,432 fp32 elements per rank took 545 us, 300 of them
+// launches and gaps.
+//
+// A send is the sink's own stores: the message is written into the next
+// rank's receive buffer (two per rank, used in turn), as a peer-to-peer write
+// over the link would, instead of into the sender's memory and then copied.
 
 __device__ __forceinline__ double ring_sparsity(uint64_t m, uint64_t nnz) {
     return m == 0 ? 1.0 : (double)(m - nnz) / (double)m;
@@ -3131,126 +3290,86 @@ __device__ __forceinline__ double ring_tau(const RingArgs& a, int r) {
     return ((r + 1) % rpn == 0 && rpn < a.P) ? a.inter : a.intra;
 }
 
-__device__ __forceinline__ void put_entry(spccl_trace_t* e, int step, int rank, int fmt, int measured, uint64_t bytes,
-                                          uint64_t nnz, double sigma) {
-    e->step = step; e->rank = rank; e->fmt = fmt; e->measured = measured;
-    e->bytes = bytes; e->nnz = nnz; e->sigma = sigma;
+// The tracked sparsity after a send: measured where it was Pici.
+__device__ __forceinline__ double ring_tracked(const RingArgs& a, const RingRank& q) {
+    return q.fmt == kFmtPici ? ring_sparsity(a.m, q.nnz) : q.sigma_prev;
 }
 
-__global__ void __launch_bounds__(256) k_ring_decide(RingArgs a) {
-    spccl_trace_t* tr = static_cast<spccl_trace_t*>(a.trace);
-    const int P = a.P;
-    const uint64_t dense_bytes = dense_msg_bytes(a.m, a.dtype);
-    for (int r = (int)(blockIdx.x * blockDim.x + threadIdx.x); r < P; r += (int)(gridDim.x * blockDim.x)) {
-        RingRank& q = a.rr[r];
-        const HeaderWords h = load_header_words(a.slots0 + (uint64_t)r * a.slot_bytes);
-        const uint32_t fmt = (uint32_t)(h.w[0] >> 32) & 0xFFFFu;
-        const uint64_t nnz = h.w[2], total = h.w[5];
-        if (a.mode == kDecideFirst) {
-            const double sg = ring_sparsity(a.m, nnz);
-            const bool dense = ring_dense(a, sg, ring_tau(a, r));
-            q.sigma0 = q.sigma_prev = sg;
-            q.in_fmt = -1;
-            q.out_fmt = dense ? kFmtDense : kFmtPici;
-            put_entry(&tr[r], 0, r, q.out_fmt, 1, dense ? dense_bytes : total, nnz, sg);
-        } else if (a.mode == kDecideStep) {
-            const int s = a.step;
-            if (s >= 2 && q.out_fmt == kFmtPici) {          // the previous send was measured
-                const double sg = ring_sparsity(a.m, nnz);
-                q.sigma_prev = sg;
-                put_entry(&tr[(s - 1) * P + r], s - 1, r, kFmtPici, 1, total, nnz, sg);
-            }
-            const HeaderWords hp = load_header_words(a.slots0 + (uint64_t)((r - 1 + P) % P) * a.slot_bytes);
-            q.in_fmt = (int32_t)((uint32_t)(hp.w[0] >> 32) & 0xFFFFu);   // what rank r receives now
-            if (s <= P - 2) {
-                const double est = q.sigma_prev * q.sigma0;
-                const bool dense = ring_dense(a, est, ring_tau(a, r));
-                q.out_fmt = dense ? kFmtDense : kFmtPici;
-                if (dense) {
-                    q.sigma_prev = est;
-                    put_entry(&tr[s * P + r], s, r, kFmtDense, 0, dense_bytes, kNnzUnknown, est);
-                }
-            } else {
-                q.out_fmt = -1;                              // the last step reduces into the output
-            }
-        } else if (a.mode == kDecideGather) {
-            const double est = q.sigma_prev * q.sigma0;
-            const bool dense = a.adaptive == 2 ? true : (a.adaptive == 0 ? false : est <= a.ag);
-            q.out_fmt = dense ? kFmtDense : kFmtPici;
-            put_entry(&tr[P * (P - 1) + r], P - 1, r, q.out_fmt, dense ? 0 : 1, dense_bytes, kNnzUnknown, est);
-        } else if (a.mode == kDecideGatherSizes) {
-            if (q.out_fmt == kFmtPici) {
-                tr[P * (P - 1) + r].bytes = total;
-                tr[P * (P - 1) + r].nnz = nnz;
-            }
-        } else {
-            (void)fmt;
-            put_entry(&tr[r], 0, r, kFmtPici, 1, total, nnz, ring_sparsity(a.m, nnz));
-        }
+__device__ __forceinline__ void put_row(RingRank* row, double sigma0, double sigma_prev, int fmt) {
+    row->sigma0 = sigma0;
+    row->sigma_prev = sigma_prev;
+    row->fmt = fmt;
+}
+
+// The dense forms of the first sends: every rank's first chunk has been
+// compressed and counted (row 0); the ranks whose sparsity is at most the
+// link's threshold encode it again.
+template <class E, bool NT>
+__global__ void __launch_bounds__(kBlockThreads) k_ring_first(RingArgs a, RankBatch rb) {
+    const int r = rb.rank[blockIdx.y];
+    RingRank* row = ring_row(a, 0) + r;
+    const double sg = ring_sparsity(a.m, row->nnz);
+    const bool dense = ring_dense(a, sg, ring_tau(a, r));
+    if (blockIdx.x == 0 && threadIdx.x == 0) put_row(row, sg, sg, dense ? kFmtDense : kFmtPici);
+    if (dense)
+        encode_dense_body<E, NT>(rb.a[blockIdx.y], rb.out[blockIdx.y], a.m, blockIdx.x,
+                                 kStreamChunk / sizeof(typename E::raw));
+}
+
+// Step a.step >= 1: rb.a = the received message, rb.b = the own chunk, rb.out =
+// the next rank's receive buffer, or the reduced chunk at the last step
+// (a.last).  One block per partition, whatever the path.
+template <class E, bool Deferred, bool NT>
+__global__ void __launch_bounds__(kBlockThreads) k_ring_step(RingArgs a, PiciSinkArgs g, RankBatch rb) {
+    __shared__ SinkLds<E> lds;
+    const uint32_t j = blockIdx.y;
+    const int r = rb.rank[j];
+    const RingRank* prev = ring_row(a, a.step - 1);
+    const RingRank q = prev[r];
+    const int in_fmt = prev[r == 0 ? a.P - 1 : r - 1].fmt;
+    bool dense = true;
+    if (!a.last) {
+        const double est = ring_tracked(a, q) * q.sigma0;               // Eq. 7
+        dense = ring_dense(a, est, ring_tau(a, r));
+        RingRank* row = ring_row(a, a.step) + r;
+        if (blockIdx.x == 0 && threadIdx.x == 0) put_row(row, q.sigma0, est, dense ? kFmtDense : kFmtPici);
+        g.nnz_out = &row->nnz;
     }
-}
-
-// ---------------------------------------------------------------------------
-// dense (+) dense -> dense, 16 bytes per lane per step (the dense ring step)
-
-template <class E>
-__device__ __forceinline__ void dense_dense_body(const uint8_t* a_hdr, const uint8_t* a, uint64_t a_cap,
-                                                 const uint8_t* b_hdr, const uint8_t* b, uint64_t b_cap,
-                                                 uint8_t* out_hdr, uint8_t* out, uint64_t n, WsCtrl* ctrl) {
-    using raw = typename E::raw;
-    __shared__ uint32_t s_ok;
-    if (threadIdx.x == 0) {
-        bool ok = true;
-        if (a_hdr) ok = ok && read_header(a_hdr, a_cap, n, E::dtype, kFmtDense).ok;
-        if (b_hdr) ok = ok && read_header(b_hdr, b_cap, n, E::dtype, kFmtDense).ok;
-        s_ok = ok;
-        if (!ok && blockIdx.x == 0) set_status(ctrl, SPCCL_ERR_CORRUPT_STREAM);
-        if (ok && blockIdx.x == 0 && out_hdr)
-            write_header(out_hdr, kFmtDense, E::dtype, n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(n, E::dtype));
+    g.a = DevOperand{rb.a[j], in_fmt == kFmtPici ? rb.a[j] : rb.a[j] + kHeaderBytes, a.slot_bytes, nullptr, 0};
+    g.b = DevOperand{nullptr, rb.b[j], a.m * sizeof(typename E::raw), nullptr, 0};
+    g.out = rb.out[j];
+    g.flags = reinterpret_cast<uint64_t*>(rb.flags[j]);
+    g.slots = rb.slots[j];
+    if (!dense) {
+        if (in_fmt == kFmtPici) to_pici_body<E, SRC_PICI, SRC_DENSE, Deferred>(g, lds);
+        else to_pici_body<E, SRC_DENSE, SRC_DENSE, Deferred>(g, lds);
+        return;
     }
-    __syncthreads();
-    if (!s_ok) return;
-    constexpr uint32_t per = 16 / sizeof(raw);
-    const bool vec_ok = ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) |
-                          reinterpret_cast<uintptr_t>(out)) & 15u) == 0;
-    const uint64_t nvec = vec_ok ? n / per : 0;
-    const uint4* av = reinterpret_cast<const uint4*>(a);
-    const uint4* bv = reinterpret_cast<const uint4*>(b);
-    uint4* ov = reinterpret_cast<uint4*>(out);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride) {
-        uint4 x = av[i], y = bv[i], z;
-        if constexpr (sizeof(raw) == 4) {
-            z.x = oplus(E{}, x.x, y.x); z.y = oplus(E{}, x.y, y.y);
-            z.z = oplus(E{}, x.z, y.z); z.w = oplus(E{}, x.w, y.w);
-        } else {
-            auto two = [](uint32_t p, uint32_t q) {
-                return oplus(E{}, p & 0xFFFFu, q & 0xFFFFu) | (oplus(E{}, p >> 16, q >> 16) << 16);
-            };
-            z.x = two(x.x, y.x); z.y = two(x.y, y.y); z.z = two(x.z, y.z); z.w = two(x.w, y.w);
-        }
-        st_stream(&ov[i], z);
+    const DenseSinkArgs d{g.a, g.b, a.last ? nullptr : g.out, a.last ? g.out : g.out + kHeaderBytes, g.n, g.T, g.ctrl};
+    if (in_fmt == kFmtPici) to_dense_body<E, SRC_PICI, SRC_DENSE>(d, lds.stage);
+    else dense_dense_body<E, NT>(d, blockIdx.x, kPartElems);
+}
+
+// The all-reduce's transition: each rank encodes its reduced chunk (rb.a) once
+// more, densely iff the estimate is at most ag_thresh (phase-aware switch).
+template <class E, bool Deferred, bool NT>
+__global__ void __launch_bounds__(kBlockThreads, sink_waves(SRC_NONE, Deferred))
+k_ring_gather(RingArgs a, PiciSinkArgs g, RankBatch rb) {
+    __shared__ SinkLds<E> lds;
+    const uint32_t j = blockIdx.y;
+    const int r = rb.rank[j];
+    const RingRank q = ring_row(a, a.step - 1)[r];
+    const double est = ring_tracked(a, q) * q.sigma0;
+    const bool dense = ring_dense(a, est, a.ag);
+    RingRank* row = ring_row(a, a.step) + r;
+    if (blockIdx.x == 0 && threadIdx.x == 0) put_row(row, q.sigma0, est, dense ? kFmtDense : kFmtPici);
+    if (dense) {
+        encode_dense_body<E, NT>(rb.a[j], rb.out[j], a.m, blockIdx.x, kPartElems);
+        return;
     }
-    // the tail (or everything, for arrays that are not 16-byte aligned)
-    const raw* ae = reinterpret_cast<const raw*>(a);
-    const raw* be = reinterpret_cast<const raw*>(b);
-    raw* oe = reinterpret_cast<raw*>(out);
-    for (uint64_t i = nvec * per + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        st_stream(&oe[i], (raw)oplus(E{}, ae[i], be[i]));
-}
-
-template <class E>
-__global__ void __launch_bounds__(256) k_dense_dense(const uint8_t* a_hdr, const uint8_t* a, uint64_t a_cap,
-                                                     const uint8_t* b_hdr, const uint8_t* b, uint64_t b_cap,
-                                                     uint8_t* out_hdr, uint8_t* out, uint64_t n, WsCtrl* ctrl) {
-    dense_dense_body<E>(a_hdr, a, a_cap, b_hdr, b, b_cap, out_hdr, out, n, ctrl);
-}
-
-template <class E>
-__global__ void __launch_bounds__(256) k_dense_dense_rb(DenseSinkArgs g, RankBatch rb) {
-    if (rank_skipped(rb, blockIdx.y)) return;
-    const DenseSinkArgs r = rank_dense(g, rb, blockIdx.y);
-    dense_dense_body<E>(r.a.hdr, r.a.data, r.a.cap, r.b.hdr, r.b.data, r.b.cap, r.out_hdr, r.out, g.n, g.ctrl);
+    g = rank_sink(g, rb, j);
+    g.nnz_out = &row->nnz;
+    to_pici_body<E, SRC_DENSE, SRC_NONE, Deferred>(g, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -3287,41 +3406,10 @@ __global__ void __launch_bounds__(256) k_copy_message(const uint8_t* src, uint64
     copy_message_body(src, src_cap, dst, dst_cap, ctrl);
 }
 
-// The sends of one ring step for a batch of ranks (grid y): rb.a -> rb.out.
+// The sends of a batch of ranks (grid y): rb.a -> rb.out.
 __global__ void __launch_bounds__(256) k_copy_message_rb(uint64_t src_cap, uint64_t dst_cap, WsCtrl* ctrl,
                                                          RankBatch rb) {
     copy_message_body(rb.a[blockIdx.y], src_cap, rb.out[blockIdx.y], dst_cap, ctrl);
-}
-
-template <class E>
-__device__ __forceinline__ void encode_dense_body(const uint8_t* src, uint8_t* out, uint64_t n) {
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        write_header(out, kFmtDense, E::dtype, n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(n, E::dtype));
-    using raw = typename E::raw;
-    const uint64_t bytes = n * sizeof(raw);
-    const bool vec_ok = (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
-    const uint64_t nvec = vec_ok ? bytes / 16 : 0;
-    const uint4* s4 = reinterpret_cast<const uint4*>(src);
-    uint4* d4 = reinterpret_cast<uint4*>(out + kHeaderBytes);
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += stride) st_stream(&d4[i], s4[i]);
-    // the tail (or everything, for a source that is not 16-byte aligned), element by element
-    const raw* se = reinterpret_cast<const raw*>(src);
-    raw* de = reinterpret_cast<raw*>(out + kHeaderBytes);
-    for (uint64_t i = nvec * 16 / sizeof(raw) + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
-        st_stream(&de[i], se[i]);
-}
-
-template <class E>
-__global__ void __launch_bounds__(256) k_encode_dense(const uint8_t* src, uint8_t* out, uint64_t n) {
-    encode_dense_body<E>(src, out, n);
-}
-
-// Dense sends of one ring step for a batch of ranks (grid y): rb.a -> rb.out.
-template <class E>
-__global__ void __launch_bounds__(256) k_encode_dense_rb(uint64_t n, RankBatch rb) {
-    if (rank_skipped(rb, blockIdx.y)) return;
-    encode_dense_body<E>(rb.a[blockIdx.y], rb.out[blockIdx.y], n);
 }
 
 __global__ void __launch_bounds__(256) k_fill_zero(uint4* p, uint64_t nvec, uint8_t* tail, uint64_t ntail) {
@@ -3505,15 +3593,20 @@ spccl_status_t launch_gather_dt(int dtype, const GatherArgs& g, int P, hipStream
     return launch_status();
 }
 
-spccl_status_t launch_dense_dense_dt(int dtype, const uint8_t* a_hdr, const uint8_t* a, uint64_t a_cap,
-                                     const uint8_t* b_hdr, const uint8_t* b, uint64_t b_cap, uint8_t* out_hdr,
-                                     uint8_t* out, uint64_t n, WsCtrl* ctrl, hipStream_t st) {
-    const uint64_t vec = n / (16 / elem_bytes(dtype));
-    dim3 grid(stream_grid(vec, 256 * 4, 8192)), block(256);
-    if (dtype == kBF16)
-        hipLaunchKernelGGL(k_dense_dense<BF16>, grid, block, 0, st, a_hdr, a, a_cap, b_hdr, b, b_cap, out_hdr, out, n, ctrl);
-    else
-        hipLaunchKernelGGL(k_dense_dense<F32>, grid, block, 0, st, a_hdr, a, a_cap, b_hdr, b, b_cap, out_hdr, out, n, ctrl);
+// One block per kStreamChunk bytes; non-temporal loads beyond the cache.
+inline uint32_t chunk_grid(uint64_t bytes) { return stream_grid(bytes, (uint32_t)kStreamChunk, 0x7FFFFFFF); }
+
+spccl_status_t launch_dense_dense_dt(int dtype, const DenseSinkArgs& g, hipStream_t st) {
+    const uint64_t bytes = g.n * elem_bytes(dtype);
+    const dim3 grid(chunk_grid(bytes)), block(kBlockThreads);
+    const bool nt = 2 * bytes >= kCacheBytes;
+    if (dtype == kBF16) {
+        if (nt) hipLaunchKernelGGL((k_dense_dense<BF16, true>), grid, block, 0, st, g);
+        else hipLaunchKernelGGL((k_dense_dense<BF16, false>), grid, block, 0, st, g);
+    } else {
+        if (nt) hipLaunchKernelGGL((k_dense_dense<F32, true>), grid, block, 0, st, g);
+        else hipLaunchKernelGGL((k_dense_dense<F32, false>), grid, block, 0, st, g);
+    }
     return launch_status();
 }
 
@@ -3526,9 +3619,16 @@ spccl_status_t launch_copy_message(const uint8_t* src, uint64_t src_cap, uint8_t
 }
 
 spccl_status_t launch_encode_dense_dt(int dtype, const uint8_t* src, uint8_t* out, uint64_t n, hipStream_t st) {
-    dim3 grid(stream_grid(n * elem_bytes(dtype) / 16, 256 * 4, 4096)), block(256);
-    if (dtype == kBF16) hipLaunchKernelGGL(k_encode_dense<BF16>, grid, block, 0, st, src, out, n);
-    else hipLaunchKernelGGL(k_encode_dense<F32>, grid, block, 0, st, src, out, n);
+    const uint64_t bytes = n * elem_bytes(dtype);
+    const dim3 grid(chunk_grid(bytes)), block(kBlockThreads);
+    const bool nt = bytes >= kCacheBytes;
+    if (dtype == kBF16) {
+        if (nt) hipLaunchKernelGGL((k_encode_dense<BF16, true>), grid, block, 0, st, src, out, n);
+        else hipLaunchKernelGGL((k_encode_dense<BF16, false>), grid, block, 0, st, src, out, n);
+    } else {
+        if (nt) hipLaunchKernelGGL((k_encode_dense<F32, true>), grid, block, 0, st, src, out, n);
+        else hipLaunchKernelGGL((k_encode_dense<F32, false>), grid, block, 0, st, src, out, n);
+    }
     return launch_status();
 }
 
@@ -3569,73 +3669,97 @@ spccl_status_t launch_sliced_batch_dt(int dtype, const SlicedBatch& b, uint32_t 
     return launch_status();
 }
 
-spccl_status_t launch_copy_sliced_batch(const SlicedBatch& b, uint32_t ranks, hipStream_t st) {
-    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks) return SPCCL_ERR_INVALID_ARG;
-    const uint64_t S = num_slices(b.base.n);
-    hipLaunchKernelGGL(k_copy_sliced_batch, dim3((unsigned)((S + kWavesPerBlock - 1) / kWavesPerBlock), ranks),
-                       dim3(kBlockThreads), 0, st, b, S);
-    return launch_status();
-}
-
 // ---- batched launches of one canonical ring step (grid y = rank) ----------
 // Grid-stride kernels give each rank a share of about 4096 blocks.
 inline uint32_t per_rank_cap(uint32_t ranks) { return ranks >= 64 ? 64u : 4096u / ranks; }
 
-template <class E, bool Deferred>
-spccl_status_t launch_to_pici_rb_k(int sa, int sb, const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks,
-                                   hipStream_t st) {
-    const dim3 grid(g.nparts, ranks), block(kBlockThreads);
-#define SPCCL_TO_PICI_RB(A, B) hipLaunchKernelGGL((k_to_pici_rb<E, A, B, Deferred>), grid, block, 0, st, g, rb)
-    if (sa == SRC_DENSE && sb == SRC_NONE) SPCCL_TO_PICI_RB(SRC_DENSE, SRC_NONE);
-    else if (sa == SRC_PICI && sb == SRC_DENSE) SPCCL_TO_PICI_RB(SRC_PICI, SRC_DENSE);
-    else if (sa == SRC_DENSE && sb == SRC_DENSE) SPCCL_TO_PICI_RB(SRC_DENSE, SRC_DENSE);
-    else return SPCCL_ERR_UNSUPPORTED;
-#undef SPCCL_TO_PICI_RB
-    return launch_status();
-}
-
-// The same choice as launch_to_pici, per rank's message.
+// Whether a rank's Pici message takes the two passes (as launch_to_pici decides).
 template <class E>
-spccl_status_t launch_to_pici_rb(int sa, int sb, const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks,
-                                 hipStream_t st) {
+bool rank_two_pass(uint32_t nparts) {
     const uint32_t bound = g_single_pass_max_parts.load(std::memory_order_relaxed);
     const uint32_t own = sizeof(typename E::raw) == 4 ? 0xFFFFFFFFu : kOneLaunchMaxPartsBF16;
-    if (g.nparts <= (own < bound ? own : bound)) return launch_to_pici_rb_k<E, false>(sa, sb, g, rb, ranks, st);
-    spccl_status_t s1 = launch_to_pici_rb_k<E, true>(sa, sb, g, rb, ranks, st);
-    if (s1 != SPCCL_OK) return s1;
-    hipLaunchKernelGGL(k_place_rb<E>, dim3((g.nparts + kPlacePer - 1) / kPlacePer, ranks), dim3(kBlockThreads), 0, st,
-                       g, rb);
+    return nparts > (own < bound ? own : bound);
+}
+
+template <class E>
+spccl_status_t place_rb(const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks, hipStream_t st) {
+    hipLaunchKernelGGL(k_place_rb<E>, dim3((g.nparts + kPlacePer - 1) / kPlacePer, ranks), dim3(kBlockThreads), 0, st, g,
+                       rb);
     return launch_status();
 }
 
 template <class E>
-spccl_status_t launch_to_dense_rb(int sa, int sb, const DenseSinkArgs& g, const RankBatch& rb, uint32_t ranks,
-                                  hipStream_t st) {
-    if (sa == SRC_DENSE && sb == SRC_DENSE) {
-        const uint64_t vec = g.n / (16 / sizeof(typename E::raw));
-        hipLaunchKernelGGL(k_dense_dense_rb<E>, dim3(stream_grid(vec, 256 * 4, per_rank_cap(ranks)), ranks), dim3(256), 0,
-                           st, g, rb);
-    } else if (sa == SRC_PICI && sb == SRC_DENSE) {
-        hipLaunchKernelGGL((k_to_dense_rb<E, SRC_PICI, SRC_DENSE>),
-                           dim3(stream_grid(g.T, kWavesPerBlock, 0x7FFFFFFF), ranks), dim3(kBlockThreads), 0, st, g, rb);
+spccl_status_t launch_compress_rb(const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks, hipStream_t st) {
+    const dim3 grid(g.nparts, ranks), block(kBlockThreads);
+    if (!rank_two_pass<E>(g.nparts)) {
+        hipLaunchKernelGGL((k_compress_rb<E, false>), grid, block, 0, st, g, rb);
+        return launch_status();
+    }
+    hipLaunchKernelGGL((k_compress_rb<E, true>), grid, block, 0, st, g, rb);
+    const spccl_status_t s1 = launch_status();
+    return s1 == SPCCL_OK ? place_rb<E>(g, rb, ranks, st) : s1;
+}
+
+template <class E, bool NT>
+spccl_status_t launch_ring_nt(int what, const RingArgs& a, PiciSinkArgs g, const RankBatch& rb, uint32_t ranks,
+                              hipStream_t st) {
+    const dim3 block(kBlockThreads);
+    if (what == kRingFirst) {
+        // only the block that writes the row where no send can be dense
+        const dim3 grid(a.adaptive == 0 ? 1u : chunk_grid(a.m * sizeof(typename E::raw)), ranks);
+        hipLaunchKernelGGL((k_ring_first<E, NT>), grid, block, 0, st, a, rb);
+        return launch_status();
+    }
+    const dim3 grid(g.nparts, ranks);
+    const bool two = rank_two_pass<E>(g.nparts) && !a.last;
+    if (what == kRingStep) {
+        if (two) hipLaunchKernelGGL((k_ring_step<E, true, NT>), grid, block, 0, st, a, g, rb);
+        else hipLaunchKernelGGL((k_ring_step<E, false, NT>), grid, block, 0, st, a, g, rb);
     } else {
-        return SPCCL_ERR_UNSUPPORTED;
+        if (two) hipLaunchKernelGGL((k_ring_gather<E, true, NT>), grid, block, 0, st, a, g, rb);
+        else hipLaunchKernelGGL((k_ring_gather<E, false, NT>), grid, block, 0, st, a, g, rb);
+    }
+    const spccl_status_t s1 = launch_status();
+    if (s1 != SPCCL_OK || !two) return s1;
+    RankBatch pb = rb;
+    pb.gate = ring_row(a, a.step);
+    g.nnz_rows = ring_row(a, a.step);
+    return place_rb<E>(g, pb, ranks, st);
+}
+
+template <class E>
+spccl_status_t launch_ring_t(int what, const RingArgs& a, const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks,
+                             hipStream_t st) {
+    const uint64_t bytes = a.m * sizeof(typename E::raw) * ranks;
+    return (what == kRingStep ? 2 : 1) * bytes >= kCacheBytes ? launch_ring_nt<E, true>(what, a, g, rb, ranks, st)
+                                                              : launch_ring_nt<E, false>(what, a, g, rb, ranks, st);
+}
+
+spccl_status_t launch_compress_rb_dt(int dtype, const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks,
+                                     hipStream_t st) {
+    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks || !g.slots) return SPCCL_ERR_INVALID_ARG;
+    return dtype == kBF16 ? launch_compress_rb<BF16>(g, rb, ranks, st) : launch_compress_rb<F32>(g, rb, ranks, st);
+}
+
+spccl_status_t launch_ring_dt(int dtype, int what, const RingArgs& a, const PiciSinkArgs& g, const RankBatch& rb,
+                              uint32_t ranks, hipStream_t st) {
+    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks || !g.slots) return SPCCL_ERR_INVALID_ARG;
+    return dtype == kBF16 ? launch_ring_t<BF16>(what, a, g, rb, ranks, st) : launch_ring_t<F32>(what, a, g, rb, ranks, st);
+}
+
+spccl_status_t launch_copy_rb_dt(int dtype, uint64_t n, const RankBatch& rb, uint32_t ranks, hipStream_t st) {
+    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks) return SPCCL_ERR_INVALID_ARG;
+    const uint64_t bytes = n * elem_bytes(dtype);
+    const dim3 grid(chunk_grid(bytes), ranks), block(kBlockThreads);
+    const bool nt = bytes * ranks >= kCacheBytes;
+    if (dtype == kBF16) {
+        if (nt) hipLaunchKernelGGL((k_copy_rb<BF16, true>), grid, block, 0, st, n, rb);
+        else hipLaunchKernelGGL((k_copy_rb<BF16, false>), grid, block, 0, st, n, rb);
+    } else {
+        if (nt) hipLaunchKernelGGL((k_copy_rb<F32, true>), grid, block, 0, st, n, rb);
+        else hipLaunchKernelGGL((k_copy_rb<F32, false>), grid, block, 0, st, n, rb);
     }
     return launch_status();
-}
-
-spccl_status_t launch_to_pici_rb_dt(int dtype, int sa, int sb, const PiciSinkArgs& g, const RankBatch& rb,
-                                    uint32_t ranks, hipStream_t st) {
-    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks || !g.slots) return SPCCL_ERR_INVALID_ARG;
-    return dtype == kBF16 ? launch_to_pici_rb<BF16>(sa, sb, g, rb, ranks, st)
-                          : launch_to_pici_rb<F32>(sa, sb, g, rb, ranks, st);
-}
-
-spccl_status_t launch_to_dense_rb_dt(int dtype, int sa, int sb, const DenseSinkArgs& g, const RankBatch& rb,
-                                     uint32_t ranks, hipStream_t st) {
-    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks) return SPCCL_ERR_INVALID_ARG;
-    return dtype == kBF16 ? launch_to_dense_rb<BF16>(sa, sb, g, rb, ranks, st)
-                          : launch_to_dense_rb<F32>(sa, sb, g, rb, ranks, st);
 }
 
 spccl_status_t launch_copy_message_rb(uint64_t src_cap, uint64_t dst_cap, WsCtrl* ctrl, const RankBatch& rb,
@@ -3644,14 +3768,6 @@ spccl_status_t launch_copy_message_rb(uint64_t src_cap, uint64_t dst_cap, WsCtrl
     const uint64_t cap = src_cap < dst_cap ? src_cap : dst_cap;
     hipLaunchKernelGGL(k_copy_message_rb, dim3(stream_grid(cap / 16, 256 * 4, per_rank_cap(ranks)), ranks), dim3(256),
                        0, st, src_cap, dst_cap, ctrl, rb);
-    return launch_status();
-}
-
-spccl_status_t launch_encode_dense_rb_dt(int dtype, uint64_t n, const RankBatch& rb, uint32_t ranks, hipStream_t st) {
-    if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks) return SPCCL_ERR_INVALID_ARG;
-    const dim3 grid(stream_grid(n * elem_bytes(dtype) / 16, 256 * 4, per_rank_cap(ranks)), ranks), block(256);
-    if (dtype == kBF16) hipLaunchKernelGGL(k_encode_dense_rb<BF16>, grid, block, 0, st, n, rb);
-    else hipLaunchKernelGGL(k_encode_dense_rb<F32>, grid, block, 0, st, n, rb);
     return launch_status();
 }
 
@@ -3670,11 +3786,6 @@ spccl_status_t launch_gather_rb_dt(int dtype, const DevOperand& part, uint64_t n
         if (K == 2) hipLaunchKernelGGL((k_gather_rb<F32, 2>), grid, block, 0, st, part, n, ctrl, rb);
         else hipLaunchKernelGGL((k_gather_rb<F32, 1>), grid, block, 0, st, part, n, ctrl, rb);
     }
-    return launch_status();
-}
-
-spccl_status_t launch_ring_decide(const RingArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_ring_decide, dim3((a.P + 255) / 256), dim3(256), 0, st, a);
     return launch_status();
 }
 

@@ -1,13 +1,16 @@
 // Ring collectives over P virtual ranks held in one GPU's memory (Sec. IV).
 //
 // Sparse sends are Pici messages or, with policy.sparse_fmt = COO, COO
-// messages (the paper runs both, Sec. IV-D).  Each rank's send / receive
-// buffers are regions of one scratch allocation;
-// a "send" is a device-side copy of the message (its size is read from the
-// header on the device).  Format decisions are made on the host, per sending
-// rank, from the nonzero counts the compressing kernels write into the
-// message headers: one stream synchronization per ring step reads all P
-// headers with a single strided copy.
+// messages (the paper runs both, Sec. IV-D).  Each rank's message buffers are
+// regions of one scratch allocation.  With Pici sends a step is one launch for
+// all ranks whose blocks decide the formats themselves, and a "send" is the
+// producing kernel's own stores into the next rank's receive buffer (an
+// all-gather hop: the receiving kernel, which expands the message, also
+// writes it on).  With COO sends a "send" is a device-side copy of the message
+// (its size is read from the header on the device) and the decisions are made
+// on the host, per sending rank, from the nonzero counts in the message
+// headers: one stream synchronization per ring step reads all P headers with a
+// single strided copy.
 //
 // Decision rule (Sec. IV-C):
 //   step 0      compress the first chunk, sigma0 = sigma_prev = measured;
@@ -32,18 +35,16 @@ using namespace spccl;
 
 namespace spccl {
 spccl_status_t launch_sliced_batch_dt(int dtype, const SlicedBatch& b, uint32_t ranks, int op, hipStream_t st);
-spccl_status_t launch_copy_sliced_batch(const SlicedBatch& b, uint32_t ranks, hipStream_t st);
-spccl_status_t launch_to_pici_rb_dt(int dtype, int sa, int sb, const PiciSinkArgs& g, const RankBatch& rb,
-                                    uint32_t ranks, hipStream_t st);
-spccl_status_t launch_to_dense_rb_dt(int dtype, int sa, int sb, const DenseSinkArgs& g, const RankBatch& rb,
-                                     uint32_t ranks, hipStream_t st);
+spccl_status_t launch_compress_rb_dt(int dtype, const PiciSinkArgs& g, const RankBatch& rb, uint32_t ranks,
+                                     hipStream_t st);
+spccl_status_t launch_ring_dt(int dtype, int what, const RingArgs& a, const PiciSinkArgs& g, const RankBatch& rb,
+                              uint32_t ranks, hipStream_t st);
+spccl_status_t launch_copy_rb_dt(int dtype, uint64_t n, const RankBatch& rb, uint32_t ranks, hipStream_t st);
 spccl_status_t launch_copy_message_rb(uint64_t src_cap, uint64_t dst_cap, WsCtrl* ctrl, const RankBatch& rb,
                                       uint32_t ranks, hipStream_t st);
-spccl_status_t launch_encode_dense_rb_dt(int dtype, uint64_t n, const RankBatch& rb, uint32_t ranks, hipStream_t st);
 spccl_status_t launch_gather_rb_dt(int dtype, const DevOperand& part, uint64_t n, WsCtrl* ctrl, const RankBatch& rb,
                                    uint32_t ranks, hipStream_t st);
 spccl_status_t launch_fill_zero(void* p, uint64_t bytes, hipStream_t st);
-spccl_status_t launch_ring_decide(const RingArgs& a, hipStream_t st);
 }  // namespace spccl
 
 namespace {
@@ -56,22 +57,24 @@ inline bool overlaps(const void* a, uint64_t an, const void* b, uint64_t bn) {
 }
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
-// Scratch of the canonical collectives: one full workspace (its control block
-// holds the status word every launch of the call reports to; the per-rank
-// calls of COO sends use the rest), then for the batched Pici launches one
-// region of look-back words and one of value slots per rank, then 3 * P
-// message buffers.
+// Scratch of the canonical collectives: for the batched Pici launches one
+// region of look-back words per rank and the ring's state; one full workspace
+// (its control block holds the status word every launch of the call reports
+// to; the per-rank calls of COO sends use the rest); one region of value
+// slots per rank; then 3 * P message buffers.  The state lies right before
+// the control block, so both come back to the host in one copy.
 struct Layout {
-    uint8_t* ws;
-    uint64_t ws_bytes;
+    uint8_t* base;
     uint8_t* flags;             // P regions of look-back words (zeroed at the start of a call)
     uint64_t flag_bytes;        // per rank
+    RingRank* rows;             // P rows of P ranks: the decisions of every send
+    uint64_t row_bytes;
+    uint8_t* ws;
+    uint64_t ws_bytes;
     uint8_t* vslots;            // P regions of value slots
     uint64_t vslot_bytes;       // per rank
     uint64_t slot_bytes;        // capacity of one message buffer
     uint8_t* slots;             // 3 * P message buffers
-    RingRank* rr;               // per rank: the device-side decision state
-    spccl_trace_t* dtrace;      // the trace, written on the device
     uint8_t* slot(int which, int r, int P) const { return slots + ((uint64_t)which * P + r) * slot_bytes; }
     uint8_t* rank_flags(int r) const { return flags + (uint64_t)r * flag_bytes; }
     uint8_t* rank_slots(int r) const { return vslots + (uint64_t)r * vslot_bytes; }
@@ -86,33 +89,31 @@ uint64_t slot_need(uint64_t msg_elems, int32_t dtype) {
 
 Layout carve(void* scratch, int32_t P, uint64_t msg_elems, int32_t dtype) {
     Layout L;
-    L.ws = static_cast<uint8_t*>(scratch);
-    L.ws_bytes = round_up(spccl_workspace_bytes(msg_elems, dtype));
-    L.flags = L.ws + L.ws_bytes;
+    L.base = L.flags = static_cast<uint8_t*>(scratch);
     L.flag_bytes = round_up(8ull * flag_words(msg_elems));
-    L.vslots = L.flags + (uint64_t)P * L.flag_bytes;
+    L.rows = reinterpret_cast<RingRank*>(L.flags + (uint64_t)P * L.flag_bytes);
+    L.row_bytes = round_up(sizeof(RingRank) * (uint64_t)P * (uint64_t)P);
+    L.ws = reinterpret_cast<uint8_t*>(L.rows) + L.row_bytes;
+    L.ws_bytes = round_up(spccl_workspace_bytes(msg_elems, dtype));
+    L.vslots = L.ws + L.ws_bytes;
     L.vslot_bytes = round_up(num_parts(msg_elems) * kPartElems * elem_bytes(dtype));
     L.slot_bytes = slot_need(msg_elems, dtype);
     L.slots = L.vslots + (uint64_t)P * L.vslot_bytes;
-    L.rr = reinterpret_cast<RingRank*>(L.slots + 3ull * (uint64_t)P * L.slot_bytes);
-    L.dtrace = reinterpret_cast<spccl_trace_t*>(reinterpret_cast<uint8_t*>(L.rr) + round_up(sizeof(RingRank) * P));
     return L;
 }
 
 uint64_t scratch_need(int32_t P, uint64_t msg_elems, int32_t dtype) {
     const Layout L = carve(nullptr, P, msg_elems, dtype);
-    const uint64_t trace_entries = (uint64_t)P * (uint64_t)(P - 1) + (uint64_t)P;
-    return (uint64_t)(reinterpret_cast<uint8_t*>(L.dtrace) - L.ws) + round_up(sizeof(spccl_trace_t) * trace_entries);
+    return (uint64_t)(L.slots - L.base) + 3ull * (uint64_t)P * L.slot_bytes;
 }
 
-// Zero the parts of the scratch that must start clear: the workspace's
-// control block, look-back words and tile indexes, and every rank's
-// look-back words (the value slots and message buffers are written before
-// they are read).
-spccl_status_t init_scratch(const Layout& L, int32_t P, uint64_t msg_elems, int32_t dtype, hipStream_t st) {
-    spccl_status_t s1 = launch_fill_zero(L.ws, spccl_workspace_min_bytes(msg_elems, dtype), st);
-    if (s1 != SPCCL_OK) return s1;
-    return launch_fill_zero(L.flags, (uint64_t)P * L.flag_bytes, st);
+// Zero the parts of the scratch that must start clear: every rank's look-back
+// words, the state and the control block, and for COO sends the workspace's
+// own look-back words and tile indexes (the value slots and message buffers
+// are written before they are read).
+spccl_status_t init_scratch(const Layout& L, bool coo, uint64_t msg_elems, int32_t dtype, hipStream_t st) {
+    return launch_fill_zero(L.base, (uint64_t)(L.ws - L.base) +
+                            (coo ? spccl_workspace_min_bytes(msg_elems, dtype) : kWsFlagsOffset), st);
 }
 
 double link_tau(const spccl_policy_t& pol, int r, int P) {
@@ -169,44 +170,35 @@ bool policy_ok(const spccl_policy_t& pol) {
     } while (0)
 
 // ---- batched ring steps, decided on the device (Pici sends) --------------
-// Every ring step launches each kernel once for all ranks that may take that
-// path (grid y = rank, up to kMaxBatchRanks per launch): the P reductions,
-// sends and expansions of a step are independent of each other.  The format
-// decisions are made on the device between the launches (k_ring_decide), and
-// each rank's blocks skip the paths its decision rules out, so the host
-// enqueues the whole collective and synchronizes once, at the end.
+// Every ring step is one launch for all ranks (grid y = rank, up to
+// kMaxBatchRanks per launch): the P reductions, sends and expansions of a step
+// are independent of each other, and each block works out its rank's decision
+// (k_ring_step), so the host enqueues the whole collective and synchronizes
+// once, at the end.  A step reads the receive buffers of one parity and writes
+// those of the other.
 
 struct RankPtrs {
     const uint8_t* a;
     const uint8_t* b;
     uint8_t* out;
+    uint8_t* slots;           // nullptr for a gather that forwards nothing
 };
 
-// The formats a batched launch is for (checked per rank on the device).
-struct Gate {
-    const RingRank* rr;       // null: every rank takes part
-    int in_fmt, out_fmt;      // -1: any
-};
-constexpr Gate kNoGate{nullptr, -1, -1};
-
-// launch(rb, count) for the given ranks in batches of up to kMaxBatchRanks,
-// each rank's pointers from ptrs(rank) and its own look-back words and slots.
+// launch(rb, count) for ranks 0 .. P - 1 in batches of up to kMaxBatchRanks,
+// each rank's pointers from ptrs(rank) and its own look-back words.
 template <class Ptrs, class Launch>
-spccl_status_t batched(const Layout& L, const std::vector<int>& ranks, Gate gate, Ptrs ptrs, Launch launch) {
-    for (size_t i = 0; i < ranks.size(); i += kMaxBatchRanks) {
-        const uint32_t cnt = (uint32_t)(ranks.size() - i < (size_t)kMaxBatchRanks ? ranks.size() - i : kMaxBatchRanks);
+spccl_status_t batched(const Layout& L, int P, Ptrs ptrs, Launch launch) {
+    for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
+        const uint32_t cnt = (uint32_t)(P - r0 < kMaxBatchRanks ? P - r0 : kMaxBatchRanks);
         RankBatch rb{};
-        rb.gate = gate.rr;
-        rb.gate_in = gate.in_fmt;
-        rb.gate_out = gate.out_fmt;
         for (uint32_t j = 0; j < cnt; j++) {
-            const int r = ranks[i + j];
+            const int r = r0 + (int)j;
             const RankPtrs q = ptrs(r);
             rb.a[j] = q.a;
             rb.b[j] = q.b;
             rb.out[j] = q.out;
             rb.flags[j] = L.rank_flags(r);
-            rb.slots[j] = L.rank_slots(r);
+            rb.slots[j] = q.slots;
             rb.rank[j] = r;
         }
         SPCCL_TRY(launch(rb, cnt));
@@ -214,16 +206,9 @@ spccl_status_t batched(const Layout& L, const std::vector<int>& ranks, Gate gate
     return SPCCL_OK;
 }
 
-// an operand whose pointer comes from the batch: an array, a Pici (or any)
-// message, a dense message
-DevOperand arr_op(uint64_t bytes) { return DevOperand{nullptr, nullptr, bytes}; }
-DevOperand msg_op(const Layout& L) { return DevOperand{L.slots, L.slots, L.slot_bytes}; }
-DevOperand dense_msg_op(const Layout& L) { return DevOperand{L.slots, L.slots + kHeaderBytes, L.slot_bytes}; }
-
-PiciSinkArgs sink_args(const Layout& L, uint64_t m, DevOperand a, DevOperand b) {
+PiciSinkArgs sink_args(const Layout& L, uint64_t m, int32_t dtype) {
     PiciSinkArgs g{};
-    g.a = a;
-    g.b = b;
+    g.a = DevOperand{nullptr, nullptr, m * elem_bytes(dtype)};    // an array, from the batch
     g.n = m;
     g.T = num_tiles(m);
     g.nparts = (uint32_t)num_parts(m);
@@ -234,29 +219,14 @@ PiciSinkArgs sink_args(const Layout& L, uint64_t m, DevOperand a, DevOperand b) 
     return g;
 }
 
-DenseSinkArgs dense_args(const Layout& L, uint64_t m, DevOperand a, DevOperand b, bool out_msg) {
-    DenseSinkArgs g{};
-    g.a = a;
-    g.b = b;
-    g.out_hdr = out_msg ? L.slots : nullptr;
-    g.out = out_msg ? L.slots + kHeaderBytes : L.slots;
-    g.n = m;
-    g.T = num_tiles(m);
-    g.ctrl = reinterpret_cast<WsCtrl*>(L.ws);
-    return g;
-}
-
-RingArgs ring_args(const Layout& L, int P, uint64_t m, int dtype, const spccl_policy_t& pol, int mode, int step) {
+RingArgs ring_args(const Layout& L, int P, uint64_t m, const spccl_policy_t& pol, int step, bool last) {
     RingArgs a{};
-    a.rr = L.rr;
-    a.trace = L.dtrace;
-    a.slots0 = L.slot(0, 0, P);
+    a.rows = L.rows;
     a.slot_bytes = L.slot_bytes;
     a.m = m;
     a.P = P;
     a.step = step;
-    a.mode = mode;
-    a.dtype = dtype;
+    a.last = last ? 1 : 0;
     a.intra = pol.intra_thresh;
     a.inter = pol.inter_thresh;
     a.ag = pol.ag_thresh;
@@ -265,128 +235,129 @@ RingArgs ring_args(const Layout& L, int P, uint64_t m, int dtype, const spccl_po
     return a;
 }
 
-// src(r) (m elements) into out(r) for the ranks whose decision is Pici
-// (compressed) and dense (a dense message); gated on the device unless gate
-// is kNoGate, when every rank compresses.
+// src(r) (m elements) of every rank compressed into out(r), its count in row
+// `step` of the state.
 template <class Src, class Out>
-spccl_status_t batched_encode(const Layout& L, const std::vector<int>& ranks, Gate gate, bool with_dense, uint64_t m,
-                              int32_t dtype, Src src, Out out, hipStream_t st) {
-    const uint64_t s = elem_bytes(dtype);
-    auto ptrs = [&](int r) { return RankPtrs{src(r), nullptr, out(r)}; };
-    const PiciSinkArgs g = sink_args(L, m, arr_op(m * s), DevOperand{});
-    Gate gp = gate;
-    if (gp.rr) gp.out_fmt = SPCCL_FMT_PICI;
-    SPCCL_TRY(batched(L, ranks, gp, ptrs, [&](const RankBatch& rb, uint32_t c) {
-        return launch_to_pici_rb_dt(dtype, SRC_DENSE, SRC_NONE, g, rb, c, st);
-    }));
-    if (with_dense && gate.rr) {
-        Gate gd = gate;
-        gd.out_fmt = SPCCL_FMT_DENSE;
-        SPCCL_TRY(batched(L, ranks, gd, ptrs, [&](const RankBatch& rb, uint32_t c) {
-            return launch_encode_dense_rb_dt(dtype, m, rb, c, st);
-        }));
-    }
-    return SPCCL_OK;
+spccl_status_t batched_compress(const Layout& L, int P, uint64_t m, int32_t dtype, int step, Src src, Out out,
+                                hipStream_t st) {
+    PiciSinkArgs g = sink_args(L, m, dtype);
+    g.nnz_rows = L.rows + (uint64_t)step * P;
+    return batched(L, P, [&](int r) { return RankPtrs{src(r), nullptr, out(r), L.rank_slots(r)}; },
+                   [&](const RankBatch& rb, uint32_t c) { return launch_compress_rb_dt(dtype, g, rb, c, st); });
 }
 
 // The reduce-scatter with Pici sends and device-side decisions: the same
-// messages, results and trace (in L.dtrace) as ring_rs.
+// messages, results and decisions (in L.rows) as ring_rs.
 spccl_status_t ring_rs_dev(void* const* send, void* const* out, int P, uint64_t n, int dtype,
                            const spccl_policy_t& pol, const Layout& L, hipStream_t st) {
     const uint64_t m = n / (uint64_t)P, s = elem_bytes(dtype);
     auto chunk = [&](int r, int c) { return static_cast<const uint8_t*>(send[r]) + (uint64_t)c * m * s; };
-    std::vector<int> all(P);
-    for (int r = 0; r < P; r++) all[r] = r;
-    WsCtrl* ctrl = reinterpret_cast<WsCtrl*>(L.ws);
-    // which paths the policy leaves open: never dense (0), always dense (2), or either
-    const bool can_dense = pol.adaptive != 0, can_pici = pol.adaptive != 2;
-    // step 0: compress every rank's first chunk into slot 0 and measure sigma0;
-    // ranks whose first send is dense encode it again
-    SPCCL_TRY(batched_encode(L, all, kNoGate, false, m, dtype, [&](int r) { return chunk(r, (r - 1 + P) % P); },
-                             [&](int r) { return L.slot(0, r, P); }, st));
-    SPCCL_TRY(launch_ring_decide(ring_args(L, P, m, dtype, pol, kDecideFirst, 0), st));
-    if (can_dense)
-        SPCCL_TRY(batched(L, all, Gate{L.rr, -1, SPCCL_FMT_DENSE},
-                          [&](int r) { return RankPtrs{chunk(r, (r - 1 + P) % P), nullptr, L.slot(0, r, P)}; },
-                          [&](const RankBatch& rb, uint32_t c) { return launch_encode_dense_rb_dt(dtype, m, rb, c, st); }));
+    auto next = [&](int r) { return (r + 1) % P; };
+    // step 0: compress every rank's first chunk into the next rank's buffer and
+    // measure sigma0; ranks whose first send is dense encode it again
+    auto first = [&](int r) { return RankPtrs{chunk(r, (r - 1 + P) % P), nullptr, L.slot(0, next(r), P), nullptr}; };
+    SPCCL_TRY(batched_compress(L, P, m, dtype, 0, [&](int r) { return first(r).a; }, [&](int r) { return first(r).out; }, st));
+    const PiciSinkArgs none = sink_args(L, m, dtype);
+    SPCCL_TRY(batched(L, P, first, [&](const RankBatch& rb, uint32_t c) {
+        return launch_ring_dt(dtype, kRingFirst, ring_args(L, P, m, pol, 0, false), none, rb, c, st);
+    }));
     for (int step = 1; step <= P - 1; step++) {
-        SPCCL_TRY(launch_ring_decide(ring_args(L, P, m, dtype, pol, kDecideStep, step), st));
-        // every send of the previous step arrives: rank r receives rank r-1's message
-        SPCCL_TRY(batched(L, all, kNoGate,
-                          [&](int r) { return RankPtrs{L.slot(0, (r - 1 + P) % P, P), nullptr, L.slot(1, r, P)}; },
-                          [&](const RankBatch& rb, uint32_t c) {
-                              return launch_copy_message_rb(L.slot_bytes, L.slot_bytes, ctrl, rb, c, st);
-                          }));
         const bool last = step == P - 1;
-        auto ptrs = [&](int r) {
-            return RankPtrs{L.slot(1, r, P), chunk(r, (r - step - 1 + 2 * P) % P),
-                            last ? static_cast<uint8_t*>(out[r]) : L.slot(0, r, P)};
-        };
-        for (int in_pici = 1; in_pici >= 0; in_pici--) {
-            // a received message is dense only where a dense send can occur
-            if (in_pici ? !can_pici : !can_dense) continue;
-            const int in_fmt = in_pici ? SPCCL_FMT_PICI : SPCCL_FMT_DENSE;
-            const DevOperand a_op = in_pici ? msg_op(L) : dense_msg_op(L);
-            const int sa = in_pici ? SRC_PICI : SRC_DENSE;
-            if (!last && can_pici) {
-                const PiciSinkArgs g = sink_args(L, m, a_op, arr_op(m * s));
-                SPCCL_TRY(batched(L, all, Gate{L.rr, in_fmt, SPCCL_FMT_PICI}, ptrs, [&](const RankBatch& rb, uint32_t c) {
-                    return launch_to_pici_rb_dt(dtype, sa, SRC_DENSE, g, rb, c, st);
-                }));
-            }
-            if (last || can_dense) {
-                const DenseSinkArgs g = dense_args(L, m, a_op, arr_op(m * s), !last);
-                const Gate gd{L.rr, in_fmt, last ? -1 : SPCCL_FMT_DENSE};
-                SPCCL_TRY(batched(L, all, gd, ptrs, [&](const RankBatch& rb, uint32_t c) {
-                    return launch_to_dense_rb_dt(dtype, sa, SRC_DENSE, g, rb, c, st);
-                }));
-            }
-        }
+        const PiciSinkArgs g = sink_args(L, m, dtype);
+        SPCCL_TRY(batched(L, P,
+                          [&](int r) {
+                              return RankPtrs{L.slot((step - 1) & 1, r, P), chunk(r, (r - step - 1 + 2 * P) % P),
+                                              last ? static_cast<uint8_t*>(out[r]) : L.slot(step & 1, next(r), P),
+                                              L.rank_slots(r)};
+                          },
+                          [&](const RankBatch& rb, uint32_t c) {
+                              return launch_ring_dt(dtype, kRingStep, ring_args(L, P, m, pol, step, last), g, rb, c, st);
+                          }));
     }
     return SPCCL_OK;
 }
 
 // All-gather of P parts of `len` elements: part q is encoded once by rank q
-// (slot 0 holds those messages, of any format), travels the ring unchanged,
-// and is expanded into out[r] + q*len by every rank r != q; each rank's own
-// part is copied from own[r] unless it already sits in place.  One copy
-// launch and one expansion launch per hop.
-spccl_status_t ring_ag_batched(void* const* own, void* const* out, int P, uint64_t len, int dtype, const Layout& L,
-                               hipStream_t st) {
+// (buffer 2 of rank q holds that message), travels the ring unchanged, and is
+// expanded into out[r] + q*len by every rank r != q; each rank's own part is
+// copied from own[r] unless it already sits in place.  Each hop is one launch
+// that expands the message and writes it on into the rank's own buffer, which
+// the next rank reads at the next hop; COO messages are copied first, by a
+// launch of their own.
+spccl_status_t ring_ag_batched(void* const* own, void* const* out, int P, uint64_t len, int dtype, bool coo,
+                               const Layout& L, hipStream_t st) {
     const uint64_t s = elem_bytes(dtype);
+    auto place = [&](int r, int q) { return static_cast<uint8_t*>(out[r]) + (uint64_t)q * len * s; };
+    RankBatch mine{};
+    uint32_t copies = 0;
     for (int r = 0; r < P; r++) {
-        uint8_t* dst = static_cast<uint8_t*>(out[r]) + (uint64_t)r * len * s;
-        if (len && dst != own[r] && hipMemcpyAsync(dst, own[r], len * s, hipMemcpyDeviceToDevice, st) != hipSuccess)
-            return SPCCL_ERR_HIP;
+        if (len && place(r, r) != own[r]) {
+            mine.a[copies] = static_cast<const uint8_t*>(own[r]);
+            mine.out[copies++] = place(r, r);
+        }
+        if (copies && (copies == (uint32_t)kMaxBatchRanks || r == P - 1)) {
+            SPCCL_TRY(launch_copy_rb_dt(dtype, len, mine, copies, st));
+            copies = 0;
+        }
     }
-    std::vector<int> all(P);
-    for (int r = 0; r < P; r++) all[r] = r;
     WsCtrl* ctrl = reinterpret_cast<WsCtrl*>(L.ws);
+    const DevOperand part{L.slots, L.slots, L.slot_bytes, nullptr, 0};
     for (int k = 0; k < P - 1; k++) {
-        const int in_slot = 1 + (k % 2), prev_slot = k == 0 ? 0 : 1 + ((k - 1) % 2);
-        SPCCL_TRY(batched(L, all, kNoGate,
-                          [&](int r) { return RankPtrs{L.slot(prev_slot, (r - 1 + P) % P, P), nullptr, L.slot(in_slot, r, P)}; },
-                          [&](const RankBatch& rb, uint32_t c) {
-                              return launch_copy_message_rb(L.slot_bytes, L.slot_bytes, ctrl, rb, c, st);
-                          }));
-        SPCCL_TRY(batched(L, all, kNoGate,
+        const int in = k == 0 ? 2 : (k - 1) & 1, on = k & 1;        // the buffers read and written at this hop
+        auto left = [&](int r) { return L.slot(in, (r - 1 + P) % P, P); };
+        if (coo)
+            SPCCL_TRY(batched(L, P, [&](int r) { return RankPtrs{left(r), nullptr, L.slot(on, r, P), nullptr}; },
+                              [&](const RankBatch& rb, uint32_t c) {
+                                  return launch_copy_message_rb(L.slot_bytes, L.slot_bytes, ctrl, rb, c, st);
+                              }));
+        SPCCL_TRY(batched(L, P,
                           [&](int r) {
-                              const int q = ((r - 1 - k) % P + P) % P;
-                              return RankPtrs{L.slot(in_slot, r, P), nullptr,
-                                              static_cast<uint8_t*>(out[r]) + (uint64_t)q * len * s};
+                              uint8_t* dst = place(r, ((r - 1 - k) % P + P) % P);
+                              if (coo) return RankPtrs{L.slot(on, r, P), nullptr, dst, nullptr};
+                              return RankPtrs{left(r), nullptr, dst, k < P - 2 ? L.slot(on, r, P) : nullptr};
                           },
                           [&](const RankBatch& rb, uint32_t c) {
-                              return launch_gather_rb_dt(dtype, msg_op(L), len, ctrl, rb, c, st);
+                              return launch_gather_rb_dt(dtype, part, len, ctrl, rb, c, st);
                           }));
     }
     return SPCCL_OK;
 }
 
-// The trace written on the device into the caller's array (entries [0, count)).
-spccl_status_t copy_trace(const Layout& L, spccl_trace_t* trace, uint64_t count, hipStream_t st) {
-    if (!trace || !count) return SPCCL_OK;
-    return hipMemcpyAsync(trace, L.dtrace, sizeof(spccl_trace_t) * count, hipMemcpyDeviceToHost, st) == hipSuccess
-               ? SPCCL_OK : SPCCL_ERR_HIP;
+// Ends a device-decided collective: its state and status word come back in one
+// copy, and the sends become trace entries (what: reduce-scatter sends, an
+// all-gather's, or both).
+enum TraceOf { kTraceRs = 1, kTraceTransition = 2, kTraceAg = 4 };
+
+spccl_status_t finish_dev(const Layout& L, int P, uint64_t m, int dtype, int what, spccl_trace_t* trace, hipStream_t st) {
+    std::vector<uint8_t> host(L.row_bytes + sizeof(uint32_t));
+    if (hipMemcpyAsync(host.data(), L.rows, host.size(), hipMemcpyDeviceToHost, st) != hipSuccess) return SPCCL_ERR_HIP;
+    if (hipStreamSynchronize(st) != hipSuccess) return SPCCL_ERR_HIP;
+    uint32_t status;
+    memcpy(&status, host.data() + L.row_bytes, sizeof(status));
+    const RingRank* rows = reinterpret_cast<const RingRank*>(host.data());
+    const uint64_t dense_bytes = dense_msg_bytes(m, dtype);
+    if ((what & kTraceRs) && trace)
+        for (int step = 0; step < P - 1; step++)
+            for (int r = 0; r < P; r++) {
+                const RingRank& q = rows[(uint64_t)step * P + r];
+                const bool pici = q.fmt == SPCCL_FMT_PICI, counted = pici || step == 0;
+                put_trace(trace, step * P + r, step, r, q.fmt, counted ? 1 : 0,
+                          pici ? pici_bytes(m, dtype, q.nnz) : dense_bytes, counted ? q.nnz : SPCCL_NNZ_UNKNOWN,
+                          pici ? sparsity(m, q.nnz) : q.sigma_prev);
+            }
+    if ((what & kTraceTransition) && trace)
+        for (int r = 0; r < P; r++) {
+            const RingRank& q = rows[(uint64_t)(P - 1) * P + r];
+            const bool pici = q.fmt == SPCCL_FMT_PICI;
+            put_trace(trace, P * (P - 1) + r, P - 1, r, q.fmt, pici ? 1 : 0, pici ? pici_bytes(m, dtype, q.nnz) : dense_bytes,
+                      pici ? q.nnz : SPCCL_NNZ_UNKNOWN, q.sigma_prev);
+        }
+    if ((what & kTraceAg) && trace)
+        for (int r = 0; r < P; r++)
+            put_trace(trace, r, 0, r, SPCCL_FMT_PICI, 1, pici_bytes(m, dtype, rows[r].nnz), rows[r].nnz,
+                      sparsity(m, rows[r].nnz));
+    if (status != SPCCL_OK) return spccl_read_status(L.ws, 1, st);      // also clears it
+    return SPCCL_OK;
 }
 
 // Reduce-scatter over the chunks; the reduced chunk r goes to out[r] (m
@@ -543,14 +514,14 @@ spccl_status_t spccl_vr_reduce_scatter(void* const* send, void* const* recv, int
     if (!policy_ok(pol)) return SPCCL_ERR_INVALID_ARG;
     hipStream_t st = as_stream(stream);
     const Layout L = carve(scratch, P, m, dtype);
-    SPCCL_TRY(init_scratch(L, P, m, dtype, st));
-    if (device_ring(pol, P)) {
+    const bool dev = device_ring(pol, P);
+    SPCCL_TRY(init_scratch(L, !dev, m, dtype, st));
+    if (dev) {
         SPCCL_TRY(ring_rs_dev(send, recv, P, n, dtype, pol, L, st));
-        SPCCL_TRY(copy_trace(L, trace, (uint64_t)P * (uint64_t)(P - 1), st));
-    } else {
-        std::vector<double> sig0, sigp;
-        SPCCL_TRY(ring_rs(send, recv, P, n, dtype, pol, L, trace, sig0, sigp, st));
+        return finish_dev(L, P, m, dtype, kTraceRs, trace, st);
     }
+    std::vector<double> sig0, sigp;
+    SPCCL_TRY(ring_rs(send, recv, P, n, dtype, pol, L, trace, sig0, sigp, st));
     return finish(L, st);
 }
 
@@ -565,23 +536,20 @@ spccl_status_t spccl_vr_all_gather(void* const* send, void* const* recv, int32_t
     if (!policy_ok(pol)) return SPCCL_ERR_INVALID_ARG;
     hipStream_t st = as_stream(stream);
     const Layout L = carve(scratch, P, n, dtype);
-    SPCCL_TRY(init_scratch(L, P, n, dtype, st));
-    if (pol.sparse_fmt == SPCCL_FMT_PICI) {
-        std::vector<int> all(P);
-        for (int q = 0; q < P; q++) all[q] = q;
-        SPCCL_TRY(batched_encode(L, all, kNoGate, false, n, dtype,
-                                 [&](int q) { return static_cast<const uint8_t*>(send[q]); },
-                                 [&](int q) { return L.slot(0, q, P); }, st));
-        SPCCL_TRY(launch_ring_decide(ring_args(L, P, n, dtype, pol, kDecideAllGather, 0), st));
-        SPCCL_TRY(copy_trace(L, trace, (uint64_t)P, st));
-    } else {
-        for (int q = 0; q < P; q++) SPCCL_TRY(compress_fmt(pol.sparse_fmt, send[q], n, dtype, L, L.slot(0, q, P), st));
-        std::vector<spccl_header_t> h;
-        SPCCL_TRY(read_headers(L, 0, P, h, st));
-        for (int q = 0; q < P; q++)
-            put_trace(trace, q, 0, q, pol.sparse_fmt, 1, h[q].total_bytes, h[q].nnz, sparsity(n, h[q].nnz));
+    const bool coo = pol.sparse_fmt != SPCCL_FMT_PICI;
+    SPCCL_TRY(init_scratch(L, coo, n, dtype, st));
+    if (!coo) {
+        SPCCL_TRY(batched_compress(L, P, n, dtype, 0, [&](int q) { return static_cast<const uint8_t*>(send[q]); },
+                                   [&](int q) { return L.slot(2, q, P); }, st));
+        SPCCL_TRY(ring_ag_batched(send, recv, P, n, dtype, false, L, st));
+        return finish_dev(L, P, n, dtype, kTraceAg, trace, st);
     }
-    SPCCL_TRY(ring_ag_batched(send, recv, P, n, dtype, L, st));
+    for (int q = 0; q < P; q++) SPCCL_TRY(compress_fmt(pol.sparse_fmt, send[q], n, dtype, L, L.slot(2, q, P), st));
+    std::vector<spccl_header_t> h;
+    SPCCL_TRY(read_headers(L, 2, P, h, st));
+    for (int q = 0; q < P; q++)
+        put_trace(trace, q, 0, q, pol.sparse_fmt, 1, h[q].total_bytes, h[q].nnz, sparsity(n, h[q].nnz));
+    SPCCL_TRY(ring_ag_batched(send, recv, P, n, dtype, true, L, st));
     return finish(L, st);
 }
 
@@ -597,44 +565,47 @@ spccl_status_t spccl_vr_all_reduce(void* const* send, void* const* recv, int32_t
     if (!policy_ok(pol)) return SPCCL_ERR_INVALID_ARG;
     hipStream_t st = as_stream(stream);
     const Layout L = carve(scratch, P, m, dtype);
-    SPCCL_TRY(init_scratch(L, P, m, dtype, st));
+    const bool dev = device_ring(pol, P);
+    SPCCL_TRY(init_scratch(L, !dev, m, dtype, st));
     // reduce-scatter straight into each rank's own chunk of its output
     std::vector<void*> chunk_out(P);
     for (int r = 0; r < P; r++) chunk_out[r] = static_cast<uint8_t*>(recv[r]) + (uint64_t)r * m * s;
-    if (device_ring(pol, P)) {
+    if (dev) {
         // the transition decided on the device from each rank's tracked sparsity
-        std::vector<int> all(P);
-        for (int r = 0; r < P; r++) all[r] = r;
         SPCCL_TRY(ring_rs_dev(send, chunk_out.data(), P, n, dtype, pol, L, st));
-        SPCCL_TRY(launch_ring_decide(ring_args(L, P, m, dtype, pol, kDecideGather, 0), st));
-        SPCCL_TRY(batched_encode(L, all, Gate{L.rr, -1, -1}, pol.adaptive != 0, m, dtype,
-                                 [&](int r) { return static_cast<const uint8_t*>(chunk_out[r]); },
-                                 [&](int r) { return L.slot(0, r, P); }, st));
-        SPCCL_TRY(launch_ring_decide(ring_args(L, P, m, dtype, pol, kDecideGatherSizes, 0), st));
-        SPCCL_TRY(copy_trace(L, trace, (uint64_t)P * (uint64_t)(P - 1) + (uint64_t)P, st));
-    } else {
-        std::vector<double> sig0, sigp;
-        SPCCL_TRY(ring_rs(send, chunk_out.data(), P, n, dtype, pol, L, trace, sig0, sigp, st));
-        // phase-aware transition: one message per rank, encoded once
-        std::vector<int> fmt(P);
-        std::vector<double> est(P);
-        for (int r = 0; r < P; r++) {
-            est[r] = sigp[r] * sig0[r];
-            const bool dense = pol.adaptive == 2 ? true : (pol.adaptive == 0 ? false : est[r] <= pol.ag_thresh);
-            fmt[r] = dense ? SPCCL_FMT_DENSE : pol.sparse_fmt;
-            if (dense) SPCCL_TRY(spccl_encode_dense(chunk_out[r], m, dtype, L.slot(0, r, P), L.slot_bytes, stream));
-            else SPCCL_TRY(compress_fmt(pol.sparse_fmt, chunk_out[r], m, dtype, L, L.slot(0, r, P), st));
-        }
-        std::vector<spccl_header_t> h;
-        SPCCL_TRY(read_headers(L, 0, P, h, st));
-        spccl_trace_t* ag_tr = trace ? trace + (uint64_t)P * (uint64_t)(P - 1) : nullptr;
-        for (int r = 0; r < P; r++) {
-            const bool sparse = fmt[r] != SPCCL_FMT_DENSE;
-            put_trace(ag_tr, r, P - 1, r, fmt[r], sparse ? 1 : 0, h[r].total_bytes,
-                      sparse ? h[r].nnz : SPCCL_NNZ_UNKNOWN, est[r]);
-        }
+        const PiciSinkArgs g = sink_args(L, m, dtype);
+        SPCCL_TRY(batched(L, P,
+                          [&](int r) {
+                              return RankPtrs{static_cast<const uint8_t*>(chunk_out[r]), nullptr, L.slot(2, r, P),
+                                              L.rank_slots(r)};
+                          },
+                          [&](const RankBatch& rb, uint32_t c) {
+                              return launch_ring_dt(dtype, kRingGather, ring_args(L, P, m, pol, P - 1, false), g, rb, c, st);
+                          }));
+        SPCCL_TRY(ring_ag_batched(chunk_out.data(), recv, P, m, dtype, false, L, st));
+        return finish_dev(L, P, m, dtype, kTraceRs | kTraceTransition, trace, st);
     }
-    SPCCL_TRY(ring_ag_batched(chunk_out.data(), recv, P, m, dtype, L, st));
+    std::vector<double> sig0, sigp;
+    SPCCL_TRY(ring_rs(send, chunk_out.data(), P, n, dtype, pol, L, trace, sig0, sigp, st));
+    // phase-aware transition: one message per rank, encoded once
+    std::vector<int> fmt(P);
+    std::vector<double> est(P);
+    for (int r = 0; r < P; r++) {
+        est[r] = sigp[r] * sig0[r];
+        const bool dense = pol.adaptive == 2 ? true : (pol.adaptive == 0 ? false : est[r] <= pol.ag_thresh);
+        fmt[r] = dense ? SPCCL_FMT_DENSE : pol.sparse_fmt;
+        if (dense) SPCCL_TRY(spccl_encode_dense(chunk_out[r], m, dtype, L.slot(2, r, P), L.slot_bytes, stream));
+        else SPCCL_TRY(compress_fmt(pol.sparse_fmt, chunk_out[r], m, dtype, L, L.slot(2, r, P), st));
+    }
+    std::vector<spccl_header_t> h;
+    SPCCL_TRY(read_headers(L, 2, P, h, st));
+    spccl_trace_t* ag_tr = trace ? trace + (uint64_t)P * (uint64_t)(P - 1) : nullptr;
+    for (int r = 0; r < P; r++) {
+        const bool sparse = fmt[r] != SPCCL_FMT_DENSE;
+        put_trace(ag_tr, r, P - 1, r, fmt[r], sparse ? 1 : 0, h[r].total_bytes,
+                  sparse ? h[r].nnz : SPCCL_NNZ_UNKNOWN, est[r]);
+    }
+    SPCCL_TRY(ring_ag_batched(chunk_out.data(), recv, P, m, dtype, true, L, st));
     return finish(L, st);
 }
 
@@ -645,7 +616,7 @@ struct SlicedLayout {
     uint8_t* ws;           // control block
     double* track;         // P trackers of S slices
     uint8_t* fmt;          // (P-1) * P * S reduce-scatter formats, then P * S all-gather formats
-    uint8_t* streams;      // 2 * P sliced streams (sent, received)
+    uint8_t* streams;      // 2 * P sliced streams: each rank's receive buffers, used in turn
     uint64_t S, sbytes, track_bytes;
     uint8_t* stream(int which, int r, int P) const { return streams + ((uint64_t)which * P + r) * sbytes; }
 };
@@ -709,13 +680,12 @@ spccl_status_t check_sliced_ranks(void* const* send, uint64_t send_elems, void* 
     return SPCCL_OK;
 }
 
-SlicedBatch make_batch(const SlicedLayout& L, uint64_t m, int32_t dtype, uint8_t* out0, const uint8_t* b0,
-                       double* track0, int32_t track_step, uint8_t* fmt0) {
+SlicedBatch make_batch(const SlicedLayout& L, uint64_t m, int32_t dtype, const uint8_t* b0, double* track0,
+                       int32_t track_step, uint8_t* fmt0) {
     SlicedBatch b{};
-    b.base = SlicedArgs{nullptr, b0, out0, m, slice_slot_bytes(dtype), 0.0, reinterpret_cast<WsCtrl*>(L.ws), track0,
-                        track_step, fmt0};
+    b.base = SlicedArgs{nullptr, b0, nullptr, m, slice_slot_bytes(dtype), 0.0, reinterpret_cast<WsCtrl*>(L.ws), track0,
+                        track_step, fmt0, nullptr};
     b.b_stride = L.sbytes;
-    b.out_stride = L.sbytes;
     b.track_stride = 2 * L.S;
     b.fmt_stride = L.S;
     return b;
@@ -724,70 +694,60 @@ SlicedBatch make_batch(const SlicedLayout& L, uint64_t m, int32_t dtype, uint8_t
 inline int batch_count(int P, int r0) { return P - r0 < kMaxBatchRanks ? P - r0 : kMaxBatchRanks; }
 
 // The sliced reduce-scatter's steps (m > 0, P > 1): every step is one launch
-// per kernel for up to kMaxBatchRanks ranks (grid y = rank), the P
-// reductions of a ring step being independent; rank r's reduced chunk lands
+// for up to kMaxBatchRanks ranks (grid y = rank), the P reductions of a ring
+// step being independent; the step's sends are its own stores, into the next
+// rank's receive buffer of the step's parity.  Rank r's reduced chunk lands
 // at out[r].  Formats go to L.fmt, step-major.
 spccl_status_t sliced_rs_steps(void* const* send, uint8_t* const* out, int32_t P, uint64_t m, int32_t dtype,
                                const spccl_policy_t& pol, const SlicedLayout& L, hipStream_t st) {
     const uint64_t s = elem_bytes(dtype);
     auto chunk = [&](int r, int c) { return static_cast<const uint8_t*>(send[r]) + (uint64_t)c * m * s; };
     auto fmt_at = [&](int step, int r) { return L.fmt + ((uint64_t)step * P + r) * L.S; };
-    for (int step = 0; step <= P - 1; step++) {
-        if (step > 0)   // the sends: rank r receives rank r-1's stream
-            for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
-                SlicedBatch c = make_batch(L, m, dtype, L.stream(1, r0, P), nullptr, nullptr, 0, nullptr);
-                for (int j = 0; j < batch_count(P, r0); j++) c.a[j] = L.stream(0, (r0 + j - 1 + P) % P, P);
-                SPCCL_TRY(launch_copy_sliced_batch(c, (uint32_t)batch_count(P, r0), st));
-            }
+    for (int step = 0; step <= P - 1; step++)
         for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
             const int cnt = batch_count(P, r0);
             const bool first = step == 0, last = step == P - 1;
             // step 0 compresses each rank's first chunk and starts its slices'
             // trackers; later steps reduce the received stream into the own
             // chunk (Eq. 7 per slice); the last one into the dense output
-            SlicedBatch b = last ? make_batch(L, m, dtype, nullptr, L.stream(1, r0, P), nullptr, 0, nullptr)
-                                 : make_batch(L, m, dtype, L.stream(0, r0, P), first ? nullptr : L.stream(1, r0, P),
-                                              L.track + 2 * L.S * r0, first ? 0 : 1, fmt_at(step, r0));
+            const uint8_t* in = first ? nullptr : L.stream((step - 1) & 1, r0, P);
+            SlicedBatch b = last ? make_batch(L, m, dtype, in, nullptr, 0, nullptr)
+                                 : make_batch(L, m, dtype, in, L.track + 2 * L.S * r0, first ? 0 : 1, fmt_at(step, r0));
             for (int j = 0; j < cnt; j++) {
                 const int r = r0 + j;
                 b.a[j] = chunk(r, (r - step - 1 + 2 * P) % P);
                 b.thresh[j] = last ? 0.0 : sliced_tau(pol, r, P);
-                if (last) b.out_dense[j] = out[r];
+                b.out[j] = last ? out[r] : L.stream(step & 1, (r + 1) % P, P);
             }
             SPCCL_TRY(launch_sliced_batch_dt(dtype, b, (uint32_t)cnt,
                                              first ? kSlicedCompress : (last ? kSlicedReduceToDense : kSlicedReduceToSliced),
                                              st));
         }
-    }
     return SPCCL_OK;
 }
 
 // The sliced all-gather's hops (n_part > 0): stream(0, r) holds rank r's
 // encoded part; rank r expands it into its own place (unless own_in_place:
-// the part is already there), then at hop k receives rank r-k's stream into
-// stream(1, r) and expands it into part r-k of recv[r].  One launch per
-// kernel and hop for up to kMaxBatchRanks ranks.
+// the part is already there), then at hop k expands the stream rank r-1 holds
+// (part r-k) into its place and writes it on into its own buffer of the other
+// parity, for the next hop.  One launch per hop for up to kMaxBatchRanks
+// ranks.
 spccl_status_t sliced_ag_hops(void* const* recv, int32_t P, uint64_t n_part, int32_t dtype, const SlicedLayout& L,
                               bool own_in_place, hipStream_t st) {
     const uint64_t s = elem_bytes(dtype);
     auto place = [&](int r, int q) { return static_cast<uint8_t*>(recv[r]) + (uint64_t)q * n_part * s; };
-    for (int k = own_in_place ? 1 : 0; k <= P - 1; k++) {
+    for (int k = own_in_place ? 1 : 0; k <= P - 1; k++)
         for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
             const int cnt = batch_count(P, r0);
-            if (k > 0) {
-                SlicedBatch c = make_batch(L, n_part, dtype, L.stream(1, r0, P), nullptr, nullptr, 0, nullptr);
-                for (int j = 0; j < cnt; j++) c.a[j] = L.stream(0, (r0 + j - k + P) % P, P);
-                SPCCL_TRY(launch_copy_sliced_batch(c, (uint32_t)cnt, st));
-            }
-            SlicedBatch e = make_batch(L, n_part, dtype, nullptr, nullptr, nullptr, 0, nullptr);
+            SlicedBatch e = make_batch(L, n_part, dtype, nullptr, nullptr, 0, nullptr);
             for (int j = 0; j < cnt; j++) {
                 const int r = r0 + j;
-                e.a[j] = k == 0 ? L.stream(0, r, P) : L.stream(1, r, P);
-                e.out_dense[j] = place(r, (r - k + P) % P);
+                e.a[j] = k == 0 ? L.stream(0, r, P) : L.stream((k - 1) & 1, (r - 1 + P) % P, P);
+                e.out[j] = place(r, (r - k + P) % P);
+                if (k > 0 && k < P - 1) e.fwd[j] = L.stream(k & 1, r, P);
             }
             SPCCL_TRY(launch_sliced_batch_dt(dtype, e, (uint32_t)cnt, kSlicedExpand, st));
         }
-    }
     return SPCCL_OK;
 }
 
@@ -845,9 +805,10 @@ spccl_status_t spccl_vr_all_gather_sliced(void* const* send, void* const* recv, 
     // every rank encodes its part once, every slice Pici (a standalone
     // all-gather does not densify)
     for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
-        SlicedBatch b = make_batch(L, n, dtype, L.stream(0, r0, P), nullptr, nullptr, 0, L.fmt + (uint64_t)r0 * L.S);
+        SlicedBatch b = make_batch(L, n, dtype, nullptr, nullptr, 0, L.fmt + (uint64_t)r0 * L.S);
         for (int j = 0; j < batch_count(P, r0); j++) {
             b.a[j] = static_cast<const uint8_t*>(send[r0 + j]);
+            b.out[j] = L.stream(0, r0 + j, P);
             b.thresh[j] = -1.0;
         }
         SPCCL_TRY(launch_sliced_batch_dt(dtype, b, (uint32_t)batch_count(P, r0), kSlicedCompress, st));
@@ -887,10 +848,10 @@ spccl_status_t spccl_vr_all_reduce_sliced(void* const* send, void* const* recv, 
     const double ag_tau = pol.adaptive == 0 ? -1.0 : (pol.adaptive == 2 ? 2.0 : pol.ag_thresh);
     uint8_t* fmt_ag_dev = L.fmt + (uint64_t)(P - 1) * P * L.S;
     for (int r0 = 0; r0 < P; r0 += kMaxBatchRanks) {
-        SlicedBatch b = make_batch(L, m, dtype, L.stream(0, r0, P), nullptr, L.track + 2 * L.S * r0, 1,
-                                   fmt_ag_dev + (uint64_t)r0 * L.S);
+        SlicedBatch b = make_batch(L, m, dtype, nullptr, L.track + 2 * L.S * r0, 1, fmt_ag_dev + (uint64_t)r0 * L.S);
         for (int j = 0; j < batch_count(P, r0); j++) {
             b.a[j] = own[r0 + j];
+            b.out[j] = L.stream(0, r0 + j, P);
             b.thresh[j] = ag_tau;
         }
         SPCCL_TRY(launch_sliced_batch_dt(dtype, b, (uint32_t)batch_count(P, r0), kSlicedCompress, st));
