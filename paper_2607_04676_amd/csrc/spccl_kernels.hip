@@ -390,14 +390,82 @@ __device__ __forceinline__ void stage_values(const typename E::raw* src, uint32_
     }
 }
 
+// The rows set in sub (this lane's column of a unit) from stage[rank ...] to
+// their places, two per round; returns the rank after them.
+template <class E>
+__device__ __forceinline__ uint32_t scatter_column(uint32_t sub, uint32_t rank, const typename E::raw* stage,
+                                                   typename E::raw* col) {
+    using raw = typename E::raw;
+    while (__any(sub != 0u)) {
+        if (sub) {
+            const uint32_t r = (uint32_t)__builtin_ctz(sub), nx = sub & (sub - 1u);
+            if (nx) {
+                const raw x = stage[rank], y = stage[rank + 1];
+                col[64 * r] = x;
+                col[64 * __builtin_ctz(nx)] = y;
+                rank += 2;
+            } else {
+                col[64 * r] = stage[rank];
+                rank++;
+            }
+            sub = nx & (nx - 1u);
+        }
+    }
+    return rank;
+}
+
+// v (+)= a Pici tile whose values are staged at vals (this lane's first at
+// vals[rank], column word w), or v = the tile (First), through a unit of LDS:
+// the values are scattered into a zeroed block of rows (4 KiB: 16 fp32 or 32
+// bf16 rows) by column, the work following the nonzeros, then every lane
+// reads its element of each row at a constant offset and adds.  Walking the
+// rows instead (is the row set in this column; if so read the next value, wait
+// for it, add) took ~13 vector instructions and an LDS round trip a row: the
+// bf16 reduce step at 90% sparsity issued 1480 vector instructions a tile.
+// With col each row is also stored as it is finished.
+template <class E>
+constexpr uint32_t unit_rows = 4096 / sizeof(typename E::raw) / 64;
+template <class E>
+constexpr uint32_t unit_elems = 64 * unit_rows<E>;
+
+template <class E, bool First>
+__device__ __forceinline__ void merge_staged(uint64_t w, uint32_t rank, typename E::raw* unit, const typename E::raw* vals,
+                                             uint32_t (&v)[64], typename E::raw* col = nullptr) {
+    using raw = typename E::raw;
+    constexpr uint32_t rows = unit_rows<E>;
+    const uint32_t l = lane_id();
+    uint4* u4 = reinterpret_cast<uint4*>(unit);
+#pragma unroll
+    for (uint32_t u = 0; u < 64 / rows; u++) {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; k++) u4[l + 64 * k] = uint4{0, 0, 0, 0};
+        asm volatile("" ::: "memory");
+        const uint32_t sub = rows == 32 ? (uint32_t)(w >> (32 * u)) : (uint32_t)(w >> (rows * u)) & ((1u << (rows & 31)) - 1u);
+        rank = scatter_column<E>(sub, rank, vals, unit + l);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (uint32_t q0 = 0; q0 < rows; q0 += 8) {          // eight rows read at a time: more held registers for nothing
+            uint32_t x[8];
+#pragma unroll
+            for (uint32_t q = 0; q < 8; q++) x[q] = unit[64 * (q0 + q) + l];
+#pragma unroll
+            for (uint32_t q = 0; q < 8; q++) {
+                const uint32_t r = rows * u + q0 + q;
+                v[r] = First ? x[q] : oplus(E{}, v[r], x[q]);
+                asm volatile("" : "+v"(v[r]));               // here, not when the row is used
+                if (col) st_stream(&col[64 * r], (raw)v[r]);
+            }
+            asm volatile("" ::: "memory");
+        }
+    }
+}
+
 // v (+)= the staged values of the columns whose words are in wm (zero for
 // the other lanes), this lane's first value at stage[rank].  Rows set in no
 // lane's word are skipped by a scalar test of the wave's OR of the words.
-// With col (this lane's column of a full output tile), each row is also
-// stored as soon as it is final, so the stores overlap the rest of the walk.
 template <class E, bool First>
 __device__ __forceinline__ void apply_staged(uint64_t wm, uint32_t rank, const typename E::raw* stage,
-                                             uint32_t (&v)[64], typename E::raw* col = nullptr) {
+                                             uint32_t (&v)[64]) {
     const uint32_t ulo = wave_or((uint32_t)wm), uhi = wave_or((uint32_t)(wm >> 32));
 #pragma unroll
     for (int r = 0; r < 64; r++) {
@@ -410,7 +478,6 @@ __device__ __forceinline__ void apply_staged(uint64_t wm, uint32_t rank, const t
                 v[r] = First ? x : oplus(E{}, v[r], x);
             }
         }
-        if (col) st_stream(&col[64 * r], (typename E::raw)v[r]);
     }
 }
 
@@ -422,11 +489,17 @@ __device__ __forceinline__ void expand_pici(PiciCols pc, const uint8_t* msg, uin
     const uint64_t w = pc.w;
     const uint32_t colpref = pc.colpref, cnt = pc.cnt;
     const raw* src = reinterpret_cast<const raw*>(msg + off_A(n)) + pc.base;
+    if (cnt <= E::cap - unit_elems<E>) {
+        stage_values<E>(src, cnt, stage + unit_elems<E>);
+        wave_lds_sync();
+        merge_staged<E, First>(w, colpref, stage, stage + unit_elems<E>, v);
+        return;
+    }
     if (First) {
 #pragma unroll
         for (int r = 0; r < 64; r++) v[r] = 0;
     }
-    // one pass over all 64 columns when the tile's values fit the stage,
+    // a denser tile row by row: one pass over all 64 columns when the tile's values fit the stage,
     // else one group of columns at a time
     const bool one = cnt <= E::cap;
     const int ngroups = one ? 1 : E::groups;
@@ -496,22 +569,18 @@ __device__ __forceinline__ bool expand_pici_early(PiciCols pc, const EarlyVals& 
                                                   typename E::raw* stage, uint32_t (&v)[64],
                                                   typename E::raw* col = nullptr) {
     using raw = typename E::raw;
-    static_assert(kEarlyVals <= E::cap, "early values fit the stage");
+    static_assert(kEarlyVals <= E::cap - unit_elems<E>, "early values fit the stage beside a unit");
     if (e.cnt != pc.cnt) {
         expand_pici<E, First>(pc, msg, n, stage, v);
         return false;
     }
     const uint32_t l = lane_id();
-    if (First) {
-#pragma unroll
-        for (int r = 0; r < 64; r++) v[r] = 0;
-    }
+    raw* vals = stage + unit_elems<E>;
 #pragma unroll
     for (int j = 0; j < kEarlySlots; j++)
-        if (l + 64u * j < pc.cnt) stage[l + 64 * j] = (raw)e.x[j];
+        if (l + 64u * j < pc.cnt) vals[l + 64 * j] = (raw)e.x[j];
     wave_lds_sync();
-    apply_staged<E, First>(pc.w, pc.colpref, stage, v, col);
-    wave_lds_sync();
+    merge_staged<E, First>(pc.w, pc.colpref, stage, vals, v, col);
     return col != nullptr;
 }
 
@@ -1240,7 +1309,7 @@ __device__ uint32_t chunk_lookback(uint64_t* flags, uint32_t nparts, uint32_t p,
 // LDS of a sink block (shared by the paths of a kernel that has several).
 template <class E>
 struct SinkLds {
-    typename E::raw stage[kWavesPerBlock][E::cap];
+    __attribute__((aligned(16))) typename E::raw stage[kWavesPerBlock][E::cap];
     typename E::raw spare[kWavesPerBlock][64];            // compact_rows' per-lane slots
     uint32_t cnt[kWavesPerBlock];
     uint32_t prefix;
@@ -2382,7 +2451,7 @@ __device__ __forceinline__ void to_dense_body(const DenseSinkArgs& g, typename E
 
 template <class E, int SA, int SB>
 __global__ void __launch_bounds__(kBlockThreads) k_to_dense(DenseSinkArgs g) {
-    __shared__ typename E::raw stage_all[kWavesPerBlock][E::cap];
+    __shared__ __attribute__((aligned(16))) typename E::raw stage_all[kWavesPerBlock][E::cap];
     to_dense_body<E, SA, SB>(g, stage_all);
 }
 
@@ -2525,30 +2594,6 @@ struct LineOut {
         lo = 0;
     }
 };
-
-// The rows set in sub (this lane's column of a unit) from stage[rank ...] to
-// their places, two per round; returns the rank after them.
-template <class E>
-__device__ __forceinline__ uint32_t scatter_column(uint32_t sub, uint32_t rank, const typename E::raw* stage,
-                                                   typename E::raw* col) {
-    using raw = typename E::raw;
-    while (__any(sub != 0u)) {
-        if (sub) {
-            const uint32_t r = (uint32_t)__builtin_ctz(sub), nx = sub & (sub - 1u);
-            if (nx) {
-                const raw x = stage[rank], y = stage[rank + 1];
-                col[64 * r] = x;
-                col[64 * __builtin_ctz(nx)] = y;
-                rank += 2;
-            } else {
-                col[64 * r] = stage[rank];
-                rank++;
-            }
-            sub = nx & (nx - 1u);
-        }
-    }
-    return rank;
-}
 
 // One tile from the LDS stage into the run: the value of each set bit of this
 // lane's column word w is stage[rank], rank counting up.  A unit is cleared,
@@ -2938,7 +2983,7 @@ __device__ __forceinline__ void compact_tile(const uint32_t (&v)[64], uint64_t w
 template <class E, bool HasB, bool OutSliced>
 __device__ __forceinline__ void sliced_slice(const SlicedArgs& g, uint64_t q) {
     using raw = typename E::raw;
-    __shared__ raw stage_all[kWavesPerBlock][E::cap];
+    __shared__ __attribute__((aligned(16))) raw stage_all[kWavesPerBlock][E::cap];
     __shared__ uint32_t s_cnt[kWavesPerBlock];
     const uint32_t wave = threadIdx.x >> 6, l = lane_id();
     raw* stage = stage_all[wave];
