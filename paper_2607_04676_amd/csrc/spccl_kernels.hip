@@ -3184,18 +3184,19 @@ __global__ void __launch_bounds__(kBlockThreads) k_copy_sliced(SlicedArgs g, uin
 // dense streams: dense (+) dense -> dense (the dense ring step), and plain
 // copies (dense messages)
 //
-// A block takes one contiguous range, 16 bytes per lane and four vectors in
-// flight per operand, and every range has a block of its own: blocks start in
-// index order, so the device works through memory as a front.  A grid capped
-// at 8192 blocks striding over the array lets the blocks drift apart and ran
-// at 4.8 TB/s (8 x 128 MiB sums) where this form runs at 6.1; a probe of plain
-// writes 4.0 against 6.7.  Vectors are aligned on the output; the operands
-// may start at any element and are then read with unaligned vector loads.
-// Beyond what the Infinity Cache holds, operands are read non-temporally
-// (256 MiB sums 137.9 -> 124.1 us); below, ordinary loads find what the
-// previous call left there.
-constexpr uint64_t kStreamChunk = 16384;           // bytes of output per block
-constexpr uint64_t kCacheBytes = 256ull << 20;     // the Infinity Cache
+// A block takes one short contiguous range, 16 bytes per lane, and every range
+// has a block of its own: blocks start in index order, so the device works
+// through memory as one narrow front.  A grid capped at 8192 blocks striding
+// over the array lets the blocks drift apart: 256 MiB sums took 152 us where
+// this form takes 124 (6.5 TB/s), dense messages 111 where it takes 87 (ranges
+// of 64 KiB: 139 and 106).  Sums take 16 KiB with four vectors in flight per
+// operand, copies 4 KiB (dense messages 92 -> 87 us against 16 KiB).
+// Vectors are aligned on the output; the operands may start at any element and
+// are then read with unaligned vector loads.  Beyond what the Infinity Cache
+// holds, operands are read non-temporally (256 MiB sums 138 -> 124 us); below,
+// ordinary loads find what the previous call left there.
+constexpr uint64_t kSumChunk = 16384, kCopyChunk = 4096;   // bytes of output per block
+constexpr uint64_t kCacheBytes = 256ull << 20;             // the Infinity Cache
 
 __device__ __forceinline__ u32x4 oplus_vec(F32, u32x4 x, u32x4 y) {
     u32x4 z;
@@ -3212,10 +3213,10 @@ __device__ __forceinline__ u32x4 oplus_vec(BF16, u32x4 x, u32x4 y) {
 }
 
 // out[e0 .. e1) = a (+) b (Two) or a, by the whole block.
-template <class E, bool Two, bool NT>
+template <class E, bool Two, bool NT, uint32_t U>
 __device__ __forceinline__ void stream_range(const uint8_t* a, const uint8_t* b, uint8_t* out, uint64_t e0, uint64_t e1) {
     using raw = typename E::raw;
-    constexpr uint32_t s = sizeof(raw), U = 4;
+    constexpr uint32_t s = sizeof(raw);
     const raw* ae = reinterpret_cast<const raw*>(a);
     const raw* be = reinterpret_cast<const raw*>(b);
     raw* oe = reinterpret_cast<raw*>(out);
@@ -3254,10 +3255,51 @@ __device__ __forceinline__ void stream_range(const uint8_t* a, const uint8_t* b,
     }
 }
 
-// Range `part` (elems elements) of a (+) b of n elements; the headers of
-// message operands are checked by every block, the output's written by one.
-template <class E, bool NT>
-__device__ __forceinline__ void dense_dense_body(const DenseSinkArgs& g, uint32_t part, uint64_t elems) {
+// body(e0, e1) over this block's share of n elements in a launch of one block
+// per partition (of kPartElems), whatever its size: ranges of 4 KiB, one vector
+// per thread, laid out so that the blocks of a group that runs at one time
+// (kFront of them) work through memory side by side.  Blocks that take their
+// 64 KiB as one range stretch the front sixteenfold: 8 x 1 GiB all-reduces of
+// mostly dense chunks took 8.55 ms, with ranges of 16 KiB 8.29, so 8.12.
+constexpr uint32_t kFront = 1024;
+template <class E, class Body>
+__device__ __forceinline__ void part_pieces(uint32_t part, uint32_t nparts, uint64_t n, Body body) {
+    constexpr uint32_t elems = 4096 / sizeof(typename E::raw), pieces = (uint32_t)(kPartElems / elems);
+    const uint32_t first = part / kFront * kFront;
+    const uint32_t width = nparts - first < kFront ? nparts - first : kFront;
+#pragma unroll 1
+    for (uint32_t i = 0; i < pieces; i++) {
+        const uint64_t e0 = ((uint64_t)first * pieces + (uint64_t)i * width + (part - first)) * elems;
+        if (e0 < n) body(e0, n - e0 < elems ? n : e0 + elems);
+    }
+}
+
+// One range of Bytes per block, U vectors in flight.
+template <class E, uint64_t Bytes, uint32_t Vecs>
+struct OneRange {
+    static constexpr uint32_t U = Vecs;
+    uint64_t n;
+    template <class Body>
+    __device__ __forceinline__ void operator()(Body body) const {
+        constexpr uint64_t elems = Bytes / sizeof(typename E::raw);
+        const uint64_t e0 = (uint64_t)blockIdx.x * elems;
+        if (e0 < n) body(e0, n - e0 < elems ? n : e0 + elems);
+    }
+};
+// The pieces of partition blockIdx.x.
+template <class E>
+struct PartRanges {
+    static constexpr uint32_t U = 1;
+    uint64_t n;
+    template <class Body>
+    __device__ __forceinline__ void operator()(Body body) const { part_pieces<E>(blockIdx.x, gridDim.x, n, body); }
+};
+
+// This block's ranges of a (+) b of n elements (ranges calls its argument with
+// each); the headers of message operands are checked by every block, the
+// output's written by block `part` 0.
+template <class E, bool NT, class Ranges>
+__device__ __forceinline__ void dense_dense_body(const DenseSinkArgs& g, uint32_t part, Ranges ranges) {
     bool ok = true;                       // the same in every thread of the grid
     if (g.a.hdr) ok = read_header(g.a.hdr, g.a.cap, g.n, E::dtype, kFmtDense).ok;
     if (g.b.hdr) ok = ok && read_header(g.b.hdr, g.b.cap, g.n, E::dtype, kFmtDense).ok;
@@ -3267,37 +3309,33 @@ __device__ __forceinline__ void dense_dense_body(const DenseSinkArgs& g, uint32_
             write_header(g.out_hdr, kFmtDense, E::dtype, g.n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(g.n, E::dtype));
     }
     if (!ok) return;
-    const uint64_t e0 = (uint64_t)part * elems;
-    if (e0 < g.n) stream_range<E, true, NT>(g.a.data, g.b.data, g.out, e0, g.n - e0 < elems ? g.n : e0 + elems);
+    ranges([&](uint64_t e0, uint64_t e1) { stream_range<E, true, NT, Ranges::U>(g.a.data, g.b.data, g.out, e0, e1); });
 }
 
 template <class E, bool NT>
 __global__ void __launch_bounds__(kBlockThreads) k_dense_dense(DenseSinkArgs g) {
-    dense_dense_body<E, NT>(g, blockIdx.x, kStreamChunk / sizeof(typename E::raw));
+    dense_dense_body<E, NT>(g, blockIdx.x, OneRange<E, kSumChunk, 4>{g.n});
 }
 
-// Range `part` of src[0 .. n) into the dense message at out.
-template <class E, bool NT>
-__device__ __forceinline__ void encode_dense_body(const uint8_t* src, uint8_t* out, uint64_t n, uint32_t part,
-                                                  uint64_t elems) {
-    if (part == 0 && threadIdx.x == 0)
+// This block's ranges of src[0 .. n) into the dense message at out.
+template <class E, bool NT, class Ranges>
+__device__ __forceinline__ void encode_dense_body(const uint8_t* src, uint8_t* out, uint64_t n, Ranges ranges) {
+    if (blockIdx.x == 0 && threadIdx.x == 0)
         write_header(out, kFmtDense, E::dtype, n, kNnzUnknown, 0, kHeaderBytes, dense_msg_bytes(n, E::dtype));
-    const uint64_t e0 = (uint64_t)part * elems;
-    if (e0 < n) stream_range<E, false, NT>(src, src, out + kHeaderBytes, e0, n - e0 < elems ? n : e0 + elems);
+    ranges([&](uint64_t e0, uint64_t e1) { stream_range<E, false, NT, Ranges::U>(src, src, out + kHeaderBytes, e0, e1); });
 }
 
 template <class E, bool NT>
 __global__ void __launch_bounds__(kBlockThreads) k_encode_dense(const uint8_t* src, uint8_t* out, uint64_t n) {
-    encode_dense_body<E, NT>(src, out, n, blockIdx.x, kStreamChunk / sizeof(typename E::raw));
+    encode_dense_body<E, NT>(src, out, n, OneRange<E, kCopyChunk, 1>{n});
 }
 
 // Plain copies of n elements for a batch of ranks (grid y): rb.a -> rb.out.
 template <class E, bool NT>
 __global__ void __launch_bounds__(kBlockThreads) k_copy_rb(uint64_t n, RankBatch rb) {
-    const uint64_t elems = kStreamChunk / sizeof(typename E::raw), e0 = (uint64_t)blockIdx.x * elems;
-    if (e0 < n)
-        stream_range<E, false, NT>(rb.a[blockIdx.y], rb.a[blockIdx.y], rb.out[blockIdx.y], e0,
-                                   n - e0 < elems ? n : e0 + elems);
+    OneRange<E, kCopyChunk, 1>{n}([&](uint64_t e0, uint64_t e1) {
+        stream_range<E, false, NT, 1>(rb.a[blockIdx.y], rb.a[blockIdx.y], rb.out[blockIdx.y], e0, e1);
+    });
 }
 
 // ---------------------------------------------------------------------------
@@ -3357,8 +3395,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_ring_first(RingArgs a, RankBa
     const bool dense = ring_dense(a, sg, ring_tau(a, r));
     if (blockIdx.x == 0 && threadIdx.x == 0) put_row(row, sg, sg, dense ? kFmtDense : kFmtPici);
     if (dense)
-        encode_dense_body<E, NT>(rb.a[blockIdx.y], rb.out[blockIdx.y], a.m, blockIdx.x,
-                                 kStreamChunk / sizeof(typename E::raw));
+        encode_dense_body<E, NT>(rb.a[blockIdx.y], rb.out[blockIdx.y], a.m, PartRanges<E>{a.m});
 }
 
 // Step a.step >= 1: rb.a = the received message, rb.b = the own chunk, rb.out =
@@ -3392,7 +3429,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_ring_step(RingArgs a, PiciSin
     }
     const DenseSinkArgs d{g.a, g.b, a.last ? nullptr : g.out, a.last ? g.out : g.out + kHeaderBytes, g.n, g.T, g.ctrl};
     if (in_fmt == kFmtPici) to_dense_body<E, SRC_PICI, SRC_DENSE>(d, lds.stage);
-    else dense_dense_body<E, NT>(d, blockIdx.x, kPartElems);
+    else dense_dense_body<E, NT>(d, blockIdx.x, PartRanges<E>{g.n});
 }
 
 // The all-reduce's transition: each rank encodes its reduced chunk (rb.a) once
@@ -3409,7 +3446,7 @@ k_ring_gather(RingArgs a, PiciSinkArgs g, RankBatch rb) {
     RingRank* row = ring_row(a, a.step) + r;
     if (blockIdx.x == 0 && threadIdx.x == 0) put_row(row, q.sigma0, est, dense ? kFmtDense : kFmtPici);
     if (dense) {
-        encode_dense_body<E, NT>(rb.a[j], rb.out[j], a.m, blockIdx.x, kPartElems);
+        encode_dense_body<E, NT>(rb.a[j], rb.out[j], a.m, PartRanges<E>{a.m});
         return;
     }
     g = rank_sink(g, rb, j);
@@ -3638,12 +3675,12 @@ spccl_status_t launch_gather_dt(int dtype, const GatherArgs& g, int P, hipStream
     return launch_status();
 }
 
-// One block per kStreamChunk bytes; non-temporal loads beyond the cache.
-inline uint32_t chunk_grid(uint64_t bytes) { return stream_grid(bytes, (uint32_t)kStreamChunk, 0x7FFFFFFF); }
+// One block per range; non-temporal loads beyond the cache.
+inline uint32_t chunk_grid(uint64_t bytes, uint64_t chunk) { return stream_grid(bytes, (uint32_t)chunk, 0x7FFFFFFF); }
 
 spccl_status_t launch_dense_dense_dt(int dtype, const DenseSinkArgs& g, hipStream_t st) {
     const uint64_t bytes = g.n * elem_bytes(dtype);
-    const dim3 grid(chunk_grid(bytes)), block(kBlockThreads);
+    const dim3 grid(chunk_grid(bytes, kSumChunk)), block(kBlockThreads);
     const bool nt = 2 * bytes >= kCacheBytes;
     if (dtype == kBF16) {
         if (nt) hipLaunchKernelGGL((k_dense_dense<BF16, true>), grid, block, 0, st, g);
@@ -3665,7 +3702,7 @@ spccl_status_t launch_copy_message(const uint8_t* src, uint64_t src_cap, uint8_t
 
 spccl_status_t launch_encode_dense_dt(int dtype, const uint8_t* src, uint8_t* out, uint64_t n, hipStream_t st) {
     const uint64_t bytes = n * elem_bytes(dtype);
-    const dim3 grid(chunk_grid(bytes)), block(kBlockThreads);
+    const dim3 grid(chunk_grid(bytes, kCopyChunk)), block(kBlockThreads);
     const bool nt = bytes >= kCacheBytes;
     if (dtype == kBF16) {
         if (nt) hipLaunchKernelGGL((k_encode_dense<BF16, true>), grid, block, 0, st, src, out, n);
@@ -3751,7 +3788,7 @@ spccl_status_t launch_ring_nt(int what, const RingArgs& a, PiciSinkArgs g, const
     const dim3 block(kBlockThreads);
     if (what == kRingFirst) {
         // only the block that writes the row where no send can be dense
-        const dim3 grid(a.adaptive == 0 ? 1u : chunk_grid(a.m * sizeof(typename E::raw)), ranks);
+        const dim3 grid(a.adaptive == 0 ? 1u : g.nparts, ranks);
         hipLaunchKernelGGL((k_ring_first<E, NT>), grid, block, 0, st, a, rb);
         return launch_status();
     }
@@ -3795,7 +3832,7 @@ spccl_status_t launch_ring_dt(int dtype, int what, const RingArgs& a, const Pici
 spccl_status_t launch_copy_rb_dt(int dtype, uint64_t n, const RankBatch& rb, uint32_t ranks, hipStream_t st) {
     if (ranks == 0 || ranks > (uint32_t)kMaxBatchRanks) return SPCCL_ERR_INVALID_ARG;
     const uint64_t bytes = n * elem_bytes(dtype);
-    const dim3 grid(chunk_grid(bytes), ranks), block(kBlockThreads);
+    const dim3 grid(chunk_grid(bytes, kCopyChunk), ranks), block(kBlockThreads);
     const bool nt = bytes * ranks >= kCacheBytes;
     if (dtype == kBF16) {
         if (nt) hipLaunchKernelGGL((k_copy_rb<BF16, true>), grid, block, 0, st, n, rb);
