@@ -277,11 +277,11 @@ def pici_sink_launches(m: int, s: int) -> int:
 
 def vr_rs_time_us(P: int, m: int, s: int, sigma0: float, pol: Policy, km: KernelModel, launch_us: float) -> dict:
     """The same reduce-scatter on one GPU with P virtual ranks and free
-    links, as the library runs it: every kernel of a ring step is one
-    launch for all ranks, with the format decisions made on the device
-    between launches, so a step costs the sum over ranks of its algorithmic
-    bytes at the op's bandwidth plus launch_us per launch.  Launches per
-    step: a decide and a copy of the received messages, then for each input
+    links: a step costs the sum over ranks of its algorithmic bytes at the
+    op's bandwidth plus launch_us per launch of a ring whose kernels each
+    cover all ranks.  The library joins a step's decision, send and sinks in
+    one launch, so its launch_us, calibrated as a ring's fixed time over this
+    count, is that of a unit and below a launch's.  Launches per step: a decide and a copy of the received messages, then for each input
     format that can occur a Pici sink (a Pici send: pici_sink_launches) and a
     dense sink (a dense send, or the last step's output); step 0 compresses
     (a Pici sink), decides and, if the policy allows dense sends, encodes them.
