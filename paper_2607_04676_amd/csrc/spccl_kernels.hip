@@ -2509,7 +2509,7 @@ __device__ __forceinline__ void copy_wave(const typename E::raw* src, typename E
     }
 }
 
-// A wave's run of dense output elements, assembled in LDS a unit (4 KiB, or less) at a
+// A wave's run of dense output elements, assembled in LDS a unit (4 KiB) at a
 // time and stored in whole 128-byte lines, 16 bytes per lane.  A tile is 4096
 // consecutive elements, so however the values reach the unit (scattered by
 // column, or by flat index), it leaves as one stream.  The output need only
@@ -2519,11 +2519,11 @@ __device__ __forceinline__ void copy_wave(const typename E::raw* src, typename E
 // part.  Row-by-row stores of unaligned rows (two part lines per 128-byte
 // row) ran at 0.6 TB/s: a sliced all-gather hop of 8 x 5,000,011 bf16
 // elements took 140 us, now 50 (with block_tiles).
-template <class E, uint32_t Elems = 4096 / sizeof(typename E::raw)>
+template <class E>
 struct LineOut {
     using raw = typename E::raw;
-    static constexpr uint32_t kElems = Elems, kLine = 128;     // elements of a unit
-    static constexpr uint32_t kBytes = kElems * sizeof(raw);
+    static constexpr uint32_t kBytes = 4096, kLine = 128;
+    static constexpr uint32_t kElems = kBytes / sizeof(raw);   // elements of a unit
     static constexpr uint32_t kRows = kElems / 64;              // tile rows of a unit
     static constexpr uint32_t kVecs = (kBytes + kLine) / 16;    // the LDS buffer
     uint4* buf;
@@ -2602,11 +2602,11 @@ struct LineOut {
 // (Walking all 64 rows and storing each one as it is finished took five vector
 // instructions a row at any sparsity: fp32 at 90% 57.8 -> 55.1 us for 256 MiB,
 // level at 99%, where the stores are the bound either way.)
-template <class E, uint32_t Elems>
-__device__ __forceinline__ void store_from_stage(LineOut<E, Elems>& out, uint64_t rem, uint64_t w, const typename E::raw* stage,
+template <class E>
+__device__ __forceinline__ void store_from_stage(LineOut<E>& out, uint64_t rem, uint64_t w, const typename E::raw* stage,
                                                  uint32_t rank, bool last) {
     using raw = typename E::raw;
-    constexpr uint32_t rows = LineOut<E, Elems>::kRows, elems = Elems;
+    constexpr uint32_t rows = LineOut<E>::kRows, elems = LineOut<E>::kElems;
 #pragma unroll 1
     for (uint32_t u = 0; u < 64 / rows; u++) {
         const uint64_t e0 = (uint64_t)u * elems;
@@ -2617,70 +2617,6 @@ __device__ __forceinline__ void store_from_stage(LineOut<E, Elems>& out, uint64_
         const bool end = e0 + elems >= rem;
         out.flush(end ? (uint32_t)(rem - e0) : elems, last && (end || u + 1 == 64 / rows));
     }
-}
-
-// One wave's LDS in the expansion, laid out in one of two ways: up to
-// kChunkVals values beside a unit of 4 KiB, or one tile of up to kMost values
-// (bf16: 2048) beside a unit of 1024 elements, the same bytes for bf16.  Half
-// the room for values left bf16 tiles between a quarter and a half full to the
-// block, one after another: the hops of the sliced all-reduce of 8 x 5,000,011
-// bf16 elements a rank (a third of them nonzero by then) took 71-77 us, the
-// whole call 951 us, now 795.  Units of 1024 elements for every bf16 tile
-// took 1.4% more at 90% sparsity, where a column of the 4 KiB unit needs fewer
-// rounds for its values.
-template <class E>
-struct ExpandLds {
-    using raw = typename E::raw;
-    static constexpr uint32_t kMost = 4096 / sizeof(raw), kUnit = 1024;
-    static constexpr uint32_t kLines = kChunkVals * sizeof(raw) / 16;       // where the 4 KiB unit starts (uint4)
-    static constexpr uint32_t kBigLines = kMost * sizeof(raw) / 16;         // where the 1024-element unit starts
-    static constexpr uint32_t kVecs = kLines + LineOut<E>::kVecs;           // per wave
-    static_assert(kBigLines + LineOut<E, kUnit>::kVecs <= kVecs, "both layouts fit");
-    // the block's layout (block_tiles): a pool for any tile, then a 1024-element unit per wave
-    static constexpr uint32_t kPool = kTileElems * sizeof(raw) / 16;
-    static_assert(kPool + kWavesPerBlock * LineOut<E, kUnit>::kVecs <= kWavesPerBlock * kVecs, "the pool fits");
-};
-
-// src[0 .. cnt), cnt <= ExpandLds::kMost, into stage and, if fwd is given,
-// there as well, with every load in flight at once.
-template <class E>
-__device__ __forceinline__ void stage_run(const typename E::raw* src, uint32_t cnt, typename E::raw* stage,
-                                          typename E::raw* fwd) {
-    using raw = typename E::raw;
-    const uint32_t l = lane_id();
-    uint32_t x[kChunkSlots];
-    auto load = [&](uint32_t (&r)[kChunkSlots], uint32_t c0) {
-#pragma unroll
-        for (int j = 0; j < kChunkSlots; j++) {
-            const uint32_t i = c0 + l + 64 * j;
-            r[j] = i < cnt ? (uint32_t)src[i] : 0u;
-        }
-    };
-    auto put = [&](const uint32_t (&r)[kChunkSlots], uint32_t c0, raw* to) {
-#pragma unroll
-        for (int j = 0; j < kChunkSlots; j++) {
-            const uint32_t i = c0 + l + 64 * j;
-            if (i < cnt) to[i] = (raw)r[j];
-        }
-    };
-    load(x, 0);
-    if constexpr (ExpandLds<E>::kMost > kChunkVals) {
-        if (cnt > kChunkVals) {
-            uint32_t y[kChunkSlots];
-            load(y, kChunkVals);
-            put(x, 0, stage);
-            put(y, kChunkVals, stage);
-            wave_lds_sync();
-            if (fwd) {
-                put(x, 0, fwd);
-                put(y, kChunkVals, fwd);
-            }
-            return;
-        }
-    }
-    put(x, 0, stage);
-    wave_lds_sync();
-    if (fwd) put(x, 0, fwd);
 }
 
 // Tiles with more values than one wave stages, left by a block's waves for
@@ -2703,20 +2639,17 @@ struct TileLds {
 };
 
 // Each such tile by the four waves together: its values fill the waves'
-// LDS as one pool (any tile), loaded coalesced with
+// stages as one pool (4 x kChunkVals values: any tile), loaded coalesced with
 // sixteen reads per thread in flight, then each wave assembles and stores a
 // quarter of its rows.  One wave alone had to stage 16 columns at a time and
 // store their elements singly, a quarter of its lanes at work: 256 MiB at 50%
 // sparsity took 376 us in bf16 and 156 us in fp32, now 117 and 109.  Called by
 // every thread of the block.
 template <class E, int K>
-__device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, uint4* lds, TileLds* c) {
+__device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename E::raw* pool, uint4* lines, TileLds* c) {
     using raw = typename E::raw;
-    using Run = LineOut<E, ExpandLds<E>::kUnit>;
-    static_assert(kWavesPerBlock * ExpandLds<E>::kUnit == kTileElems && kBlockThreads * 16 == kTileElems, "a quarter per wave");
+    static_assert(kWavesPerBlock * kChunkVals == kTileElems && kBlockThreads * 16 == kTileElems, "the pool holds any tile");
     const uint32_t wave = threadIdx.x >> 6, l = lane_id();
-    raw* pool = reinterpret_cast<raw*>(lds);
-    uint4* lines = lds + ExpandLds<E>::kPool + wave * Run::kVecs;
     bool any = false;
 #pragma unroll
     for (int k = 0; k < K; k++) any = any || d.cnt[k] != 0u;
@@ -2760,7 +2693,7 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, uint4* ld
             __syncthreads();           // the pool is filled; c may be written again
             const uint32_t e0 = 1024u * wave;
             if (cnt && e0 < rem) {
-                Run run;
+                LineOut<E> run;
                 run.start(lines, out + e0);
                 raw* col = run.clear() + l;
                 scatter_column<E>((uint32_t)(w >> (16 * wave)) & 0xFFFFu,
@@ -2827,11 +2760,9 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
 template <class E, int K>
 __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* d, uint32_t fmt, uint64_t nnz,
                                              uint64_t n, uint64_t T, uint64_t t0, typename E::raw* out,
-                                             uint4* lds, WsCtrl* ctrl, DenseTiles<E, K>& dense, uint8_t* fwd) {
+                                             typename E::raw* stage, uint4* lines, WsCtrl* ctrl,
+                                             DenseTiles<E, K>& dense, uint8_t* fwd) {
     using raw = typename E::raw;
-    using Lds = ExpandLds<E>;
-    raw* stage = reinterpret_cast<raw*>(lds);
-    uint4* lines = lds + Lds::kLines;
     const uint32_t l = lane_id();
     const uint64_t g_n = n, g_T = T;
     if (fmt == (uint32_t)kFmtCoo) {
@@ -2890,9 +2821,28 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
         // valid tiles chain (base + cnt == next == the next tile's base)
         if (kfit == k && c.ok && (c.base - cbase[0]) + c.cnt <= kChunkVals) kfit = k + 1;
     }
-    const bool big0 = ccnt[0] > kChunkVals && ccnt[0] <= Lds::kMost;      // the first tile staged alone
-    const uint32_t chunk = big0 ? ccnt[0] : kfit ? (cbase[kfit - 1] - cbase[0]) + ccnt[kfit - 1] : 0u;
-    stage_run<E>(A + cbase[0], chunk, stage, fwd ? fA + cbase[0] : nullptr);
+    const uint32_t chunk = kfit ? (cbase[kfit - 1] - cbase[0]) + ccnt[kfit - 1] : 0u;
+    {
+        uint32_t x[kChunkSlots];
+#pragma unroll
+        for (int j = 0; j < kChunkSlots; j++) {
+            const uint32_t i = l + 64 * j;
+            x[j] = i < chunk ? (uint32_t)A[cbase[0] + i] : 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < kChunkSlots; j++) {
+            const uint32_t i = l + 64 * j;
+            if (i < chunk) stage[i] = (raw)x[j];
+        }
+        wave_lds_sync();
+        if (fwd) {
+#pragma unroll
+            for (int j = 0; j < kChunkSlots; j++) {
+                const uint32_t i = l + 64 * j;
+                if (i < chunk) fA[cbase[0] + i] = (raw)x[j];
+            }
+        }
+    }
     if (fwd) {
         uint64_t* fB = reinterpret_cast<uint64_t*>(fwd + kHeaderBytes);
         uint32_t* fI = reinterpret_cast<uint32_t*>(fwd + off_I(g_n));
@@ -2923,20 +2873,15 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
         if (cnt <= kChunkVals) {
             if (k >= kfit) {
                 wave_lds_sync();
-                stage_run<E>(A + cbase[k], cnt, stage, fwd ? fA + cbase[k] : nullptr);
+                stage_values<E>(A + cbase[k], cnt, stage);
+                wave_lds_sync();
+                if (fwd)
+                    for (uint32_t i = l; i < cnt; i += 64) fA[cbase[k] + i] = stage[i];
             }
             if (!running) run.start(lines, out + t * kTileElems);
             const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
             store_from_stage<E>(run, rem, w, stage, k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], last);
             running = !last;
-        } else if (cnt <= Lds::kMost) {
-            if (k > 0) {
-                wave_lds_sync();
-                stage_run<E>(A + cbase[k], cnt, stage, fwd ? fA + cbase[k] : nullptr);
-            }
-            LineOut<E, Lds::kUnit> own;
-            own.start(lds + Lds::kBigLines, out + t * kTileElems);
-            store_from_stage<E>(own, rem, w, stage, cpref[k], true);
         } else {
             dense.w[k] = w;                       // left for the block
             dense.pref[k] = cpref[k];
@@ -2953,7 +2898,8 @@ template <class E, int K>
 __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_part, uint64_t n, uint64_t T,
                                             WsCtrl* ctrl, uint8_t* fwd) {
     using raw = typename E::raw;
-    __shared__ uint4 lds[kWavesPerBlock * ExpandLds<E>::kVecs];
+    __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
+    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
     __shared__ TileLds tile;
     __shared__ uint32_t s_ok, s_fmt;
     __shared__ uint64_t s_nnz;
@@ -2973,8 +2919,8 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
     raw* out = reinterpret_cast<raw*>(out_part);
     const uint8_t* d = op.hdr ? op.hdr + kHeaderBytes : op.data;
     DenseTiles<E, K> dense{};
-    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, lds + wave * ExpandLds<E>::kVecs, ctrl, dense, fwd);
-    block_tiles<E, K>(dense, lds, &tile);
+    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], lines_all[wave], ctrl, dense, fwd);
+    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
 }
 
 template <class E, int K>
@@ -3163,7 +3109,8 @@ template <class E>
 __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
     using raw = typename E::raw;
     constexpr uint32_t K = kTilesPerPart / kExpandWavesPerSlice;
-    __shared__ uint4 lds[kWavesPerBlock * ExpandLds<E>::kVecs];
+    __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
+    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
     __shared__ TileLds tile;
     const uint32_t wave = threadIdx.x >> 6;
     const uint64_t wq = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
@@ -3179,12 +3126,12 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
                 if (lane_id() == 0) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
             } else {
                 expand_tiles<E, K>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
-                                   reinterpret_cast<raw*>(g.out) + base, lds + wave * ExpandLds<E>::kVecs, g.ctrl, dense,
+                                   reinterpret_cast<raw*>(g.out) + base, stage_all[wave], lines_all[wave], g.ctrl, dense,
                                    g.fwd ? g.fwd + q * g.slot : nullptr);
             }
         }
     }
-    block_tiles<E, K>(dense, lds, &tile);
+    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
 }
 
 template <class E>
