@@ -124,18 +124,20 @@ __device__ __forceinline__ void wave_lds_sync() {
 }
 
 // Bit r set iff v[r] is nonzero.  Each half is built as a doubling chain
-// from its top row down (one compare and one add-with-carry per row, written
-// out so that the compiler keeps no per-row constants live).
+// from its top row down: min(v, 1) is the row's bit, shifted in by the next
+// instruction (written out so that the compiler keeps no per-row constants
+// live).  Both write vector registers only.  A compare and an add with carry
+// take as many instructions, but gfx950 needs two wait states between a vector
+// write of a condition register and a vector read of it, which the compiler
+// fills in its own code and cannot see inside an asm block.
 __device__ __forceinline__ uint64_t nonzero_rows(const uint32_t (&v)[64]) {
-    uint32_t hi = 0, lo = 0;
+    uint32_t hi = 0, lo = 0, bit;
 #pragma unroll
     for (int r = 63; r >= 32; r--)
-        asm volatile("v_cmp_ne_u32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-                     : "+v"(hi) : "v"(v[r]) : "vcc");
+        asm volatile("v_min_u32_e32 %1, 1, %2\n\tv_lshl_or_b32 %0, %0, 1, %1" : "+v"(hi), "=&v"(bit) : "v"(v[r]));
 #pragma unroll
     for (int r = 31; r >= 0; r--)
-        asm volatile("v_cmp_ne_u32_e32 vcc, 0, %1\n\tv_addc_co_u32_e32 %0, vcc, %0, %0, vcc"
-                     : "+v"(lo) : "v"(v[r]) : "vcc");
+        asm volatile("v_min_u32_e32 %1, 1, %2\n\tv_lshl_or_b32 %0, %0, 1, %1" : "+v"(lo), "=&v"(bit) : "v"(v[r]));
     return ((uint64_t)hi << 32) | lo;
 }
 
