@@ -283,15 +283,18 @@ spccl_status_t ring_rs_dev(void* const* send, void* const* out, int P, uint64_t 
 // copied from own[r] unless it already sits in place.  Each hop is one launch
 // that expands the message and writes it on into the rank's own buffer, which
 // the next rank reads at the next hop; COO messages are copied first, by a
-// launch of their own.
+// launch of their own.  Parts of no elements are already gathered: a hop
+// writes a message on tile by tile, so it would forward nothing and the next
+// one read a buffer that no launch wrote.
 spccl_status_t ring_ag_batched(void* const* own, void* const* out, int P, uint64_t len, int dtype, bool coo,
                                const Layout& L, hipStream_t st) {
+    if (len == 0) return SPCCL_OK;
     const uint64_t s = elem_bytes(dtype);
     auto place = [&](int r, int q) { return static_cast<uint8_t*>(out[r]) + (uint64_t)q * len * s; };
     RankBatch mine{};
     uint32_t copies = 0;
     for (int r = 0; r < P; r++) {
-        if (len && place(r, r) != own[r]) {
+        if (place(r, r) != own[r]) {
             mine.a[copies] = static_cast<const uint8_t*>(own[r]);
             mine.out[copies++] = place(r, r);
         }
