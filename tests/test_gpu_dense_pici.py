@@ -1,12 +1,13 @@
 """Dense (+) Pici -> Pici (Sec. IV-B, reduction with fill-in as in Sec. I)
 against the oracle byte for byte, on tiles built around the choices the sink
 makes per tile: how many Pici values a column holds (up to six are merged
-sparsely, more take the row-wise merge), the union of both operands against
-the LDS stage (at the limit the sparse merge runs, one past it the row-wise
-one), exact cancellations where both operands are present, stored zeros in
-the Pici values (they read as absent and send the tile to the row-wise
-merge), tiles with too many values to be read early, empty operands and a
-ragged last tile; fp32 and bf16, both operand orders, both workspace sizes."""
+sparsely, more through a unit of LDS), the union of both operands against the
+LDS stage (at the limit the sparse merge runs, one past it the other one), exact
+cancellations where both operands are present, stored zeros in the Pici values
+(they read as absent and rule out the sparse merge), tiles with too many values
+to be read early, empty operands and a ragged last tile; fp32 and bf16, both
+operand orders, both workspace sizes.  (The counts where the other merge changes
+its form: test_gpu_merge_edges.py.)"""
 import numpy as np
 import pytest
 
