@@ -55,9 +55,9 @@ METRIC = "dense-equivalent GB/s (and % of HBM peak) for Pici compress/decompress
 
 # ops that launch exactly one kernel, and that kernel's name in profiles
 SINGLE_KERNEL_OPS = {
-    "decompress": "k_gather<F32, 2>",
+    "decompress": "k_gather<F32, 2, true>",
     "reduce_dense_pici_to_dense": "k_to_dense<F32, 1, 2>",
-    "gather_expand": "k_gather<F32, 2>",
+    "gather_expand": "k_gather<F32, 2, true>",
     "send": "k_copy_message",
 }
 TAU_INTRA = 0.6          # the paper's intra-node threshold for Pici (Sec. IV-C)

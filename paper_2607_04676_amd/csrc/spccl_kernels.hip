@@ -155,6 +155,8 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) {
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(p));
 }
 
+constexpr uint64_t kCacheBytes = 256ull << 20;             // the Infinity Cache
+
 // 16 bytes from any element address (unaligned vector loads).
 template <bool NT>
 __device__ __forceinline__ u32x4 ld_vec(const uint8_t* p) {
@@ -425,8 +427,9 @@ __device__ __forceinline__ uint32_t scatter_column(uint32_t sub, uint32_t rank, 
 // for it, add) took ~13 vector instructions and an LDS round trip a row: the
 // bf16 reduce step at 90% sparsity issued 1480 vector instructions a tile.
 // With col each row is also stored as it is finished.
+constexpr uint32_t kUnitBytes = 4096;
 template <class E>
-constexpr uint32_t unit_rows = 4096 / sizeof(typename E::raw) / 64;
+constexpr uint32_t unit_rows = kUnitBytes / sizeof(typename E::raw) / 64;
 template <class E>
 constexpr uint32_t unit_elems = 64 * unit_rows<E>;
 
@@ -564,7 +567,7 @@ __device__ __forceinline__ EarlyVals fetch_early(const uint8_t* msg, uint64_t ca
 
 // v (+)= the tile from its early values when they cover it (the checked
 // count equals the early range), else from the message as expand_pici does.
-// With col (see apply_staged) the rows of an early tile are also stored;
+// With col (see merge_staged) the rows of an early tile are also stored;
 // returns whether they were.
 template <class E, bool First>
 __device__ __forceinline__ bool expand_pici_early(PiciCols pc, const EarlyVals& e, const uint8_t* msg, uint64_t n,
@@ -1302,12 +1305,6 @@ __device__ uint32_t chunk_lookback(uint64_t* flags, uint32_t nparts, uint32_t p,
 // ---------------------------------------------------------------------------
 // Pici sink: out = Pici(srcA (+) srcB).
 
-// Deferred = false: one launch; each partition finds its global offset with
-// chunk_lookback and writes its values in place.
-// Deferred = true: first of two passes; each partition publishes its
-// aggregate, writes B and the tile offsets relative to the partition, and
-// parks its compacted values in its own worst-case slot of the workspace,
-// never waiting on another block; k_place then moves each slot into place.
 // LDS of a sink block (shared by the paths of a kernel that has several).
 template <class E>
 struct SinkLds {
@@ -1317,6 +1314,12 @@ struct SinkLds {
     uint32_t prefix;
 };
 
+// Deferred = false: one launch; each partition finds its global offset with
+// chunk_lookback and writes its values in place.
+// Deferred = true: first of two passes; each partition publishes its
+// aggregate, writes B and the tile offsets relative to the partition, and
+// parks its compacted values in its own worst-case slot of the workspace,
+// never waiting on another block; k_place then moves each slot into place.
 template <class E, int SA, int SB, bool Deferred>
 __device__ __forceinline__ void to_pici_body(const PiciSinkArgs& g, SinkLds<E>& lds) {
     using raw = typename E::raw;
@@ -2457,20 +2460,6 @@ __global__ void __launch_bounds__(kBlockThreads) k_to_dense(DenseSinkArgs g) {
     to_dense_body<E, SA, SB>(g, stage_all);
 }
 
-// Expansion of P parts (all-gather receive side and decompress): the format
-// of each message (dense, Pici or COO) is read from its header on the
-// device.
-//
-// Each wave expands K consecutive tiles of one part and issues its reads
-// before its first store: the K tiles' column words and offsets, then, in one
-// go, the values of as many leading tiles as fit kChunkVals (their value
-// ranges are contiguous), held in registers and staged in LDS; then it writes
-// the dense tiles.  On this architecture one counter tracks both loads and
-// stores, so a read that has to be waited for after a store also waits for
-// that store; with the reads in front the writes stream and the read latency
-// is paid once per K tiles.  Tiles that do not fit are expanded one at a
-// time (stage their values, then write), and tiles holding more than
-// kChunkVals values by the whole block (block_tiles).
 // `cnt` elements from src to dst and, if fwd is given, to fwd as well, by one
 // wave: 16 bytes per lane, eight loads in flight before their stores, vectors
 // aligned on the destination.  A forwarded run whose two destinations are
@@ -2524,9 +2513,7 @@ __device__ __forceinline__ void copy_wave(const typename E::raw* src, typename E
 template <class E>
 struct LineOut {
     using raw = typename E::raw;
-    static constexpr uint32_t kBytes = 4096, kLine = 128;
-    static constexpr uint32_t kElems = kBytes / sizeof(raw);   // elements of a unit
-    static constexpr uint32_t kRows = kElems / 64;              // tile rows of a unit
+    static constexpr uint32_t kBytes = kUnitBytes, kLine = 128;
     static constexpr uint32_t kVecs = (kBytes + kLine) / 16;    // the LDS buffer
     uint4* buf;
     uint8_t* line;        // where buf goes: the line that holds the unit's first element
@@ -2601,14 +2588,14 @@ struct LineOut {
 // lane's column word w is stage[rank], rank counting up.  A unit is cleared,
 // each lane writes its column's values at their rows, and the unit is stored:
 // the work follows the nonzeros, and the stores are 1 KiB per instruction.
-// (Walking all 64 rows and storing each one as it is finished took five vector
-// instructions a row at any sparsity: fp32 at 90% 57.8 -> 55.1 us for 256 MiB,
-// level at 99%, where the stores are the bound either way.)
+// (Walking all 64 rows and storing each one as it is finished, as store_rows
+// does, takes five vector instructions a row at any sparsity and part lines
+// where the output starts inside one, but half the LDS: see expand_rows.)
 template <class E>
 __device__ __forceinline__ void store_from_stage(LineOut<E>& out, uint64_t rem, uint64_t w, const typename E::raw* stage,
                                                  uint32_t rank, bool last) {
     using raw = typename E::raw;
-    constexpr uint32_t rows = LineOut<E>::kRows, elems = LineOut<E>::kElems;
+    constexpr uint32_t rows = unit_rows<E>, elems = unit_elems<E>;
 #pragma unroll 1
     for (uint32_t u = 0; u < 64 / rows; u++) {
         const uint64_t e0 = (uint64_t)u * elems;
@@ -2621,6 +2608,71 @@ __device__ __forceinline__ void store_from_stage(LineOut<E>& out, uint64_t rem, 
     }
 }
 
+// R rows of a tile (rem elements, the whole of them if rem is 64 R), each stored
+// as the walk over them finishes it (values as in store_from_stage).
+template <class E, bool NT, int R>
+__device__ __forceinline__ void walk_rows(typename E::raw* out, uint32_t rem, uint64_t w, const typename E::raw* stage,
+                                          uint32_t rank) {
+    using raw = typename E::raw;
+    const uint32_t l = lane_id();
+    raw* col = out + l;
+    auto put = [&](int r, raw v) {
+        if constexpr (NT) st_stream(&col[64 * r], v);
+        else col[64 * r] = v;
+    };
+    if (rem == 64u * R) {
+#pragma unroll 8
+        for (int r = 0; r < R; r++) {
+            raw v = 0;
+            if ((w >> r) & 1ull) { v = stage[rank]; rank++; }
+            put(r, v);
+        }
+    } else {
+#pragma unroll 8
+        for (int r = 0; r < R; r++) {
+            raw v = 0;
+            if ((w >> r) & 1ull) { v = stage[rank]; rank++; }
+            if (64u * r + l < rem) put(r, v);
+        }
+    }
+}
+
+// stream: past the caches, where a row is whole lines (part lines written past
+// them are slow: 256 MiB at 99% from one element past a line takes 83 us, and
+// 51 through the caches).
+template <class E, int R>
+__device__ __forceinline__ void store_rows(typename E::raw* out, uint32_t rem, uint64_t w, const typename E::raw* stage,
+                                           uint32_t rank, bool stream) {
+    if (stream && (reinterpret_cast<uintptr_t>(out) & (LineOut<E>::kLine - 1)) == 0)
+        walk_rows<E, true, R>(out, rem, w, stage, rank);
+    else
+        walk_rows<E, false, R>(out, rem, w, stage, rank);
+}
+
+// What the waves share of the tile at hand.
+struct TileLds {
+    uint64_t w[64];
+    uint32_t pref[64];
+    uint64_t src, out, fwd;
+    uint32_t cnt, rem;
+};
+
+// LDS of an expanding block.  Rows: tiles are stored row by row (store_rows),
+// and only COO tiles use the lines' buffer, which then is the wave's stage;
+// otherwise a wave has both.
+template <class E, bool Rows>
+struct ExpandLds {
+    using raw = typename E::raw;
+    static_assert(!Rows || kChunkVals * sizeof(raw) == LineOut<E>::kBytes, "the stage and a line hold a unit");
+    __attribute__((aligned(16))) raw stage[kWavesPerBlock][kChunkVals + (Rows ? LineOut<E>::kLine / sizeof(raw) : 0)];
+    uint4 own[Rows ? 1 : kWavesPerBlock][Rows ? 1 : LineOut<E>::kVecs];
+    TileLds tile;
+    __device__ __forceinline__ uint4* lines(uint32_t wave) {
+        if constexpr (Rows) return reinterpret_cast<uint4*>(stage[wave]);
+        else return own[wave];
+    }
+};
+
 // Tiles with more values than one wave stages, left by a block's waves for
 // the whole block (block_tiles): up to K per wave; cnt = 0 where there is none.
 template <class E, int K>
@@ -2632,24 +2684,18 @@ struct DenseTiles {
     typename E::raw* fwd[K];          // where its values are forwarded to (nullptr: not)
 };
 
-// What the waves share of the tile at hand.
-struct TileLds {
-    uint64_t w[64];
-    uint32_t pref[64];
-    uint64_t src, out, fwd;
-    uint32_t cnt, rem;
-};
-
 // Each such tile by the four waves together: its values fill the waves'
 // stages as one pool (4 x kChunkVals values: any tile), loaded coalesced with
 // sixteen reads per thread in flight, then each wave assembles and stores a
 // quarter of its rows.  One wave alone had to stage 16 columns at a time and
 // store their elements singly, a quarter of its lanes at work: 256 MiB at 50%
-// sparsity took 376 us in bf16 and 156 us in fp32, now 117 and 109.  Called by
+// sparsity took 356 us in bf16 and 157 us in fp32, now 119 and 71.  Called by
 // every thread of the block.
-template <class E, int K>
-__device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename E::raw* pool, uint4* lines, TileLds* c) {
+template <class E, int K, bool Rows>
+__device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, ExpandLds<E, Rows>& lds) {
     using raw = typename E::raw;
+    raw* pool = lds.stage[0];
+    TileLds* c = &lds.tile;
     static_assert(kWavesPerBlock * kChunkVals == kTileElems && kBlockThreads * 16 == kTileElems, "the pool holds any tile");
     const uint32_t wave = threadIdx.x >> 6, l = lane_id();
     bool any = false;
@@ -2695,12 +2741,18 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, typename 
             __syncthreads();           // the pool is filled; c may be written again
             const uint32_t e0 = 1024u * wave;
             if (cnt && e0 < rem) {
-                LineOut<E> run;
-                run.start(lines, out + e0);
-                raw* col = run.clear() + l;
-                scatter_column<E>((uint32_t)(w >> (16 * wave)) & 0xFFFFu,
-                                  pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)), pool, col);
-                run.flush(rem - e0 < 1024u ? rem - e0 : 1024u, true);
+                const uint32_t left = rem - e0 < 1024u ? rem - e0 : 1024u;
+                if constexpr (Rows) {
+                    store_rows<E, 16>(out + e0, left, w >> (16 * wave), pool,
+                                      pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)), true);
+                } else {
+                    LineOut<E> run;
+                    run.start(lds.lines(wave), out + e0);
+                    raw* col = run.clear() + l;
+                    scatter_column<E>((uint32_t)(w >> (16 * wave)) & 0xFFFFu,
+                                      pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)), pool, col);
+                    run.flush(left, true);
+                }
             }
         }
     }
@@ -2720,7 +2772,7 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
                                               uint64_t t0, uint64_t tend, uint64_t n, typename E::raw* out,
                                               uint4* lines) {
     using raw = typename E::raw;
-    constexpr uint32_t elems = LineOut<E>::kElems;
+    constexpr uint32_t elems = unit_elems<E>;
     const uint32_t l = lane_id();
     LineOut<E> run;
     run.start(lines, out + t0 * kTileElems);
@@ -2758,12 +2810,13 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
 // forwarded: the message itself (Pici or dense) is also written there, each
 // wave its tiles' parts, while it is at hand (an all-gather hop used to copy
 // the message first and then read the copy).  One wave; all reads before the
-// first store (see k_gather).
-template <class E, int K>
+// first store (see k_gather).  Rows: tiles are stored row by row, past the
+// caches unless cached is set and no read is waited for after the stores.
+template <class E, int K, bool Rows>
 __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* d, uint32_t fmt, uint64_t nnz,
                                              uint64_t n, uint64_t T, uint64_t t0, typename E::raw* out,
                                              typename E::raw* stage, uint4* lines, WsCtrl* ctrl,
-                                             DenseTiles<E, K>& dense, uint8_t* fwd) {
+                                             DenseTiles<E, K>& dense, uint8_t* fwd, bool cached) {
     using raw = typename E::raw;
     const uint32_t l = lane_id();
     const uint64_t g_n = n, g_T = T;
@@ -2772,7 +2825,7 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
         // neighbouring waves meet exactly), its entries checked (inside the
         // wave's tiles, below n, strictly increasing: as they are loaded when
         // they fit one chunk, else in a pass of their own first), then the
-        // tiles assembled in LDS a quarter at a time (coo_tiles_lds).
+        // tiles assembled in LDS a unit at a time (coo_tiles_lds).
         const uint32_t* J = reinterpret_cast<const uint32_t*>(msg + kHeaderBytes);
         const raw* V = reinterpret_cast<const raw*>(msg + coo_off_V(nnz));
         const uint64_t tend = t0 + K < g_T ? t0 + K : g_T;
@@ -2880,10 +2933,15 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
                 if (fwd)
                     for (uint32_t i = l; i < cnt; i += 64) fA[cbase[k] + i] = stage[i];
             }
-            if (!running) run.start(lines, out + t * kTileElems);
-            const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
-            store_from_stage<E>(run, rem, w, stage, k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], last);
-            running = !last;
+            if constexpr (Rows) {
+                store_rows<E, 64>(out + t * kTileElems, (uint32_t)(rem < kTileElems ? rem : kTileElems), w, stage,
+                                  k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], !(cached && kfit == K));
+            } else {
+                if (!running) run.start(lines, out + t * kTileElems);
+                const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
+                store_from_stage<E>(run, rem, w, stage, k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], last);
+                running = !last;
+            }
         } else {
             dense.w[k] = w;                       // left for the block
             dense.pref[k] = cpref[k];
@@ -2896,13 +2954,25 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
     }
 }
 
-template <class E, int K>
+// Expansion of P parts (all-gather receive side and decompress): the format
+// of each message (dense, Pici or COO) is read from its header on the
+// device.
+//
+// Each wave expands K consecutive tiles of one part and issues its reads
+// before its first store: the K tiles' column words and offsets, then, in one
+// go, the values of as many leading tiles as fit kChunkVals (their value
+// ranges are contiguous), held in registers and staged in LDS; then it writes
+// the dense tiles.  On this architecture one counter tracks both loads and
+// stores, so a read that has to be waited for after a store also waits for
+// that store; with the reads in front the writes stream and the read latency
+// is paid once per K tiles.  Tiles that do not fit are expanded one at a
+// time (stage their values, then write), and tiles holding more than
+// kChunkVals values by the whole block (block_tiles).
+template <class E, int K, bool Rows>
 __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_part, uint64_t n, uint64_t T,
-                                            WsCtrl* ctrl, uint8_t* fwd) {
+                                            WsCtrl* ctrl, uint8_t* fwd, bool cached) {
     using raw = typename E::raw;
-    __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
-    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
-    __shared__ TileLds tile;
+    __shared__ ExpandLds<E, Rows> lds;
     __shared__ uint32_t s_ok, s_fmt;
     __shared__ uint64_t s_nnz;
     const uint32_t wave = threadIdx.x >> 6;
@@ -2921,14 +2991,24 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
     raw* out = reinterpret_cast<raw*>(out_part);
     const uint8_t* d = op.hdr ? op.hdr + kHeaderBytes : op.data;
     DenseTiles<E, K> dense{};
-    if (t0 < T) expand_tiles<E, K>(op.data, d, s_fmt, s_nnz, n, T, t0, out, stage_all[wave], lines_all[wave], ctrl, dense, fwd);
-    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
+    if (t0 < T)
+        expand_tiles<E, K, Rows>(op.data, d, s_fmt, s_nnz, n, T, t0, out, lds.stage[wave], lds.lines(wave), ctrl, dense,
+                                 fwd, cached);
+    block_tiles<E, K, Rows>(dense, lds);
 }
 
-template <class E, int K>
-__global__ void __launch_bounds__(kBlockThreads) k_gather(GatherArgs g) {
-    gather_body<E, K>(g.part[blockIdx.y], g.out + (uint64_t)blockIdx.y * g.n * sizeof(typename E::raw), g.n, g.T,
-                      g.ctrl, nullptr);
+// Pairs of tiles are held to five waves per SIMD where that spills nothing: bf16,
+// and fp32 stored row by row (94 registers; 100 ran four waves: two fp32 parts of
+// 68 MiB at 70% 47 -> 34 us).  A bf16 tile per wave takes 92 by itself, the LDS of
+// fp32 in whole lines fits four, and the sliced kernels spill at five (2^27 bf16
+// at 90% 58.6 -> 64.1 us).
+constexpr int expand_waves(size_t s, int K, bool rows) { return rows || (s == 2 && K == 2) ? 5 : 1; }
+
+template <class E, int K, bool Rows>
+__global__ void __launch_bounds__(kBlockThreads, expand_waves(sizeof(typename E::raw), K, Rows)) k_gather(GatherArgs g) {
+    const uint64_t part = g.n * sizeof(typename E::raw);
+    gather_body<E, K, Rows>(g.part[blockIdx.y], g.out + blockIdx.y * part, g.n, g.T, g.ctrl, nullptr,
+                            gridDim.y * part <= kCacheBytes);
 }
 
 // One all-gather hop for a batch of ranks (grid y): each rank expands the
@@ -2936,7 +3016,8 @@ __global__ void __launch_bounds__(kBlockThreads) k_gather(GatherArgs g) {
 // rb.slots, its own buffer, for the next hop (nullptr: not).
 template <class E, int K>
 __global__ void __launch_bounds__(kBlockThreads) k_gather_rb(DevOperand part, uint64_t n, WsCtrl* ctrl, RankBatch rb) {
-    gather_body<E, K>(rebase(part, rb.a[blockIdx.y]), rb.out[blockIdx.y], n, num_tiles(n), ctrl, rb.slots[blockIdx.y]);
+    gather_body<E, K, false>(rebase(part, rb.a[blockIdx.y]), rb.out[blockIdx.y], n, num_tiles(n), ctrl,
+                             rb.slots[blockIdx.y], false);
 }
 
 // ---------------------------------------------------------------------------
@@ -3107,13 +3188,11 @@ __global__ void __launch_bounds__(kBlockThreads) k_sliced_batch(SlicedBatch b) {
 // check is flagged and not written.
 constexpr uint32_t kExpandWavesPerSlice = 2;
 
-template <class E>
+template <class E, bool Rows, bool Forward>
 __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
     using raw = typename E::raw;
     constexpr uint32_t K = kTilesPerPart / kExpandWavesPerSlice;
-    __shared__ raw stage_all[kWavesPerBlock][kChunkVals];
-    __shared__ uint4 lines_all[kWavesPerBlock][LineOut<E>::kVecs];
-    __shared__ TileLds tile;
+    __shared__ ExpandLds<E, Rows> lds;
     const uint32_t wave = threadIdx.x >> 6;
     const uint64_t wq = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
     const uint64_t q = wq / kExpandWavesPerSlice, t0 = K * (wq % kExpandWavesPerSlice);
@@ -3127,24 +3206,24 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
             if (!h.ok || h.fmt == (uint32_t)kFmtCoo) {        // slices are Pici or dense
                 if (lane_id() == 0) set_status(g.ctrl, SPCCL_ERR_CORRUPT_STREAM);
             } else {
-                expand_tiles<E, K>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
-                                   reinterpret_cast<raw*>(g.out) + base, stage_all[wave], lines_all[wave], g.ctrl, dense,
-                                   g.fwd ? g.fwd + q * g.slot : nullptr);
+                expand_tiles<E, K, Rows>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
+                                         reinterpret_cast<raw*>(g.out) + base, lds.stage[wave], lds.lines(wave), g.ctrl,
+                                         dense, Forward && g.fwd ? g.fwd + q * g.slot : nullptr, g.n * sizeof(raw) <= kCacheBytes);
             }
         }
     }
-    block_tiles<E, K>(dense, stage_all[0], lines_all[wave], &tile);
+    block_tiles<E, K, Rows>(dense, lds);
 }
 
-template <class E>
+template <class E, bool Rows>
 __global__ void __launch_bounds__(kBlockThreads) k_expand_sliced(SlicedArgs g) {
-    expand_slice<E>(g);
+    expand_slice<E, Rows, false>(g);
 }
 
 // One all-gather hop's expansions for a batch of virtual ranks (blockIdx.y).
 template <class E>
 __global__ void __launch_bounds__(kBlockThreads) k_expand_sliced_batch(SlicedBatch b) {
-    expand_slice<E>(batch_rank(b, blockIdx.y));
+    expand_slice<E, false, true>(batch_rank(b, blockIdx.y));
 }
 
 // The virtual-rank send of a sliced stream: each slot's header.total_bytes,
@@ -3198,7 +3277,6 @@ __global__ void __launch_bounds__(kBlockThreads) k_copy_sliced(SlicedArgs g, uin
 // holds, operands are read non-temporally (256 MiB sums 138 -> 124 us); below,
 // ordinary loads find what the previous call left there.
 constexpr uint64_t kSumChunk = 16384, kCopyChunk = 4096;   // bytes of output per block
-constexpr uint64_t kCacheBytes = 256ull << 20;             // the Infinity Cache
 
 __device__ __forceinline__ u32x4 oplus_vec(F32, u32x4 x, u32x4 y) {
     u32x4 z;
@@ -3657,18 +3735,49 @@ spccl_status_t launch_to_coo_dt(int dtype, int sa, int sb, const PiciSinkArgs& g
     return dtype == kBF16 ? launch_to_coo<BF16>(sa, sb, g, st) : launch_to_coo<F32>(sa, sb, g, st);
 }
 
-// Tiles per wave of the expansion: two once that still leaves enough waves
-// to fill the chip (about 8192 resident), else one.  Four tiles per wave
-// measured the same at 99% sparsity and 10% slower at 90% (their values no
-// longer fit one staged chunk), one tile per wave 5-10% slower at 99%.
+// Whether an fp32 expansion of P parts of `bytes` each stores its tiles row by
+// row (store_rows) instead of through LDS in whole lines (LineOut).  Lines
+// double a block's LDS: four blocks fit a CU, 1024 the chip, which is 64 MiB at
+// a tile per wave.  Up to there lines are as fast or faster (16 MiB at 99%, cold
+// 10.2 us against 11.6; sliced, 32 MiB 10.5 against 12.6); beyond, the rows are
+// (80 MiB at 90% 23.4 -> 18.0 us, 256 MiB at 99% 52.2 -> 48.0, sliced 55.0 ->
+// 45.5, 512 MiB at 90% 105.8 -> 101).  They leave the chip past the caches,
+// unless the output fits the Infinity Cache and no wave reads again after its
+// first store: 256 MiB at 99% then takes 47.4 us instead of 50.5 (at 80%, where
+// the waves do read again, 63 against 53).  Outputs that start inside a line are
+// written in part lines and take the rows up to 128 MiB (80 MiB at 90% 25.1 ->
+// 18.5 us, but 512 MiB at 80% 115 -> 139).  A bf16 row is one line: in whole
+// lines it is the faster at any size.
+inline bool expand_rows(const uint8_t* out, uint64_t bytes, uint64_t P) {
+    const bool whole = ((reinterpret_cast<uintptr_t>(out) | (P > 1 ? bytes : 0)) & 127u) == 0;
+    return P * bytes > (64ull << 20) && (whole || P * bytes <= (128ull << 20));
+}
+
+// Tiles per wave of an expansion: two where that still leaves more waves than
+// fit the chip (from 16384 tiles).  Four measured the same at 99% sparsity and
+// 10% slower at 90% (their values no longer fit one staged chunk), one 5-10%
+// slower at 99%.  bf16 also takes two where one would run the chip's waves a
+// little more than once: 48 MiB at 99% 15.4 -> 12.9 us, 90% 15.7 -> 13.8 (but 96
+// MiB at 50%, two rounds of pairs, 49.8 -> 60).  Rows of fp32 always take two.
+constexpr uint64_t kResidentWaves = 5 * 1024;      // five per SIMD
+
 template <class E>
 void launch_gather_k(const GatherArgs& g, int P, hipStream_t st) {
     const uint64_t tiles = g.T * (uint64_t)P;
-    const int K = tiles >= 2 * 8192 ? 2 : 1;
     dim3 block(kBlockThreads);
-    dim3 grid(stream_grid(g.T, kWavesPerBlock * K, 0x7FFFFFFF), (unsigned)P);
-    if (K == 2) hipLaunchKernelGGL((k_gather<E, 2>), grid, block, 0, st, g);
-    else hipLaunchKernelGGL((k_gather<E, 1>), grid, block, 0, st, g);
+    auto grid = [&](uint32_t K) { return dim3(stream_grid(g.T, kWavesPerBlock * K, 0x7FFFFFFF), (unsigned)P); };
+    if constexpr (sizeof(typename E::raw) == 4) {
+        if (expand_rows(g.out, g.n * sizeof(typename E::raw), (uint64_t)P)) {
+            hipLaunchKernelGGL((k_gather<E, 2, true>), grid(2), block, 0, st, g);
+            return;
+        }
+        if (tiles >= 2 * 8192) hipLaunchKernelGGL((k_gather<E, 2, false>), grid(2), block, 0, st, g);
+        else hipLaunchKernelGGL((k_gather<E, 1, false>), grid(1), block, 0, st, g);
+    } else {
+        const bool two = tiles >= 2 * 8192 || (tiles > kResidentWaves && tiles <= 2 * kResidentWaves);
+        if (two) hipLaunchKernelGGL((k_gather<E, 2, false>), grid(2), block, 0, st, g);
+        else hipLaunchKernelGGL((k_gather<E, 1, false>), grid(1), block, 0, st, g);
+    }
 }
 
 spccl_status_t launch_gather_dt(int dtype, const GatherArgs& g, int P, hipStream_t st) {
@@ -3723,8 +3832,16 @@ void launch_sliced_t(const SlicedArgs& g, int op, hipStream_t st) {
     if (op == kSlicedCompress) hipLaunchKernelGGL((k_sliced<E, false, true>), dim3(S), block, 0, st, g);
     else if (op == kSlicedReduceToSliced) hipLaunchKernelGGL((k_sliced<E, true, true>), dim3(S), block, 0, st, g);
     else if (op == kSlicedReduceToDense) hipLaunchKernelGGL((k_sliced<E, true, false>), dim3(S), block, 0, st, g);
-    else hipLaunchKernelGGL(k_expand_sliced<E>,
-                            dim3((S * kExpandWavesPerSlice + kWavesPerBlock - 1) / kWavesPerBlock), block, 0, st, g);
+    else {
+        const dim3 grid((S * kExpandWavesPerSlice + kWavesPerBlock - 1) / kWavesPerBlock);
+        if constexpr (sizeof(typename E::raw) == 4) {
+            if (expand_rows(g.out, g.n * sizeof(typename E::raw), 1)) {
+                hipLaunchKernelGGL((k_expand_sliced<E, true>), grid, block, 0, st, g);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_expand_sliced<E, false>), grid, block, 0, st, g);
+    }
 }
 
 spccl_status_t launch_sliced_dt(int dtype, const SlicedArgs& g, int op, hipStream_t st) {
