@@ -275,41 +275,41 @@ def pici_sink_launches(m: int, s: int) -> int:
     return 1 if s == 4 or -(-m // 16384) <= 2048 else 2
 
 
+def vr_rs_launches(P: int, m: int, s: int) -> int:
+    """Launches of the canonical reduce-scatter on one GPU, whatever formats
+    the policy chooses: the scratch's fill, then for every 32 ranks the first
+    compression and the dense forms of the first sends, each later send (a Pici
+    sink, whose place pass is issued for dense sends as well) and the step that
+    completes the chunks."""
+    if P == 1:
+        return 0
+    sink = pici_sink_launches(m, s)
+    return 1 + -(-P // 32) * (sink + 1 + (P - 2) * sink + 1)
+
+
 def vr_rs_time_us(P: int, m: int, s: int, sigma0: float, pol: Policy, km: KernelModel, launch_us: float) -> dict:
     """The same reduce-scatter on one GPU with P virtual ranks and free
     links: a step costs the sum over ranks of its algorithmic bytes at the
-    op's bandwidth plus launch_us per launch of a ring whose kernels each
-    cover all ranks.  The library joins a step's decision, send and sinks in
-    one launch, so its launch_us, calibrated as a ring's fixed time over this
-    count, is that of a unit and below a launch's.  Launches per step: a decide and a copy of the received messages, then for each input
-    format that can occur a Pici sink (a Pici send: pici_sink_launches) and a
-    dense sink (a dense send, or the last step's output); step 0 compresses
-    (a Pici sink), decides and, if the policy allows dense sends, encodes them.
-    Returns the total and its two terms (us) and the launch count."""
+    op's bandwidth (a send is the producing kernel's own store) plus launch_us
+    per launch (vr_rs_launches).  Returns the total and its two terms (us) and
+    the launch count."""
     if P == 1:
         return {"total_us": 0.0, "bytes_us": 0.0, "launch_us": 0.0, "launches": 0}
-    can_dense, can_sparse = pol.adaptive != 0, pol.adaptive != 2
     bw = lambda op, sg: km.ops[op].bandwidth(sg) * 1e3        # bytes per us
     fmts, _, true, _, _ = replay_rs(P, sigma0, pol)
     dense_chunk = m * s
     bytes_us = 0.0
-    sink = pici_sink_launches(m, s)
-    launches = sink + 1 + (1 if can_dense else 0)
+    launches = vr_rs_launches(P, m, s)
     for r in range(P):
         bytes_us += (dense_chunk + message_bytes(m, s, pol.sparse_fmt, sigma0)) / bw("compress", sigma0)
         if fmts[0][r] == FMT_DENSE:
             bytes_us += (2 * dense_chunk) / bw("copy", sigma0)
     for step in range(1, P):
         last = step == P - 1
-        launches += 2
-        for fin_ok in (can_sparse, can_dense):
-            if fin_ok:
-                launches += (sink if (not last and can_sparse) else 0) + (1 if (last or can_dense) else 0)
         sig_in, sig_out = true[step - 1], sigma0 ** (step + 1)
         for r in range(P):
             fin = fmts[step - 1][(r - 1) % P]
             in_b = message_bytes(m, s, fin, sig_in)
-            bytes_us += 2 * in_b / bw("copy", sig_in)
             fout = FMT_DENSE if last else fmts[step][r]
             if fout == FMT_DENSE:
                 op = "dense_dense" if fin == FMT_DENSE else "to_dense"

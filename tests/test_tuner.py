@@ -86,34 +86,32 @@ def test_recommend_is_a_grid_point_and_reports_the_paper_pair():
         assert w["best_us"] <= w["paper_us"] and w["best_us"] <= w["dense_us"] + 1e-9
 
 
-@pytest.mark.parametrize("s,m,adaptive,launches", [(4, 1 << 16, 1, 43), (4, 1 << 16, 0, 23), (4, 1 << 16, 2, 24),
-                                                     (2, 1 << 16, 1, 43), (2, 2049 * 16384, 1, 56),
-                                                     (2, 2049 * 16384, 0, 30), (2, 2049 * 16384, 2, 25)])
-def test_one_gpu_ring_launches_follow_the_policy(s, m, adaptive, launches):
-    """The one-GPU ring issues, per step, a decide and a copy, then for each
-    input format the policy allows a Pici sink (a sparse send: one launch, or
-    a count and a place pass for bf16 messages above 2048 partitions) and a
-    dense sink (a dense send or the last step); step 0 compresses, decides
-    and, if dense sends are allowed, encodes them."""
+@pytest.mark.parametrize("P,s,m,launches", [(8, 4, 1 << 16, 10), (8, 2, 1 << 16, 10), (8, 2, 2049 * 16384, 17),
+                                            (2, 4, 1 << 16, 4), (33, 4, 1 << 16, 69), (1, 4, 1 << 16, 0)])
+@pytest.mark.parametrize("adaptive", [0, 1, 2])
+def test_one_gpu_ring_launches(P, s, m, launches, adaptive):
+    """The one-GPU ring issues a fill, then per 32 ranks: the compression of
+    the first chunks (a Pici sink: one launch, or a count and a place pass for
+    bf16 messages above 2048 partitions), their dense forms, P - 2 sending
+    steps (a Pici sink each) and the last step; the policy changes none."""
     km = T.KernelModel.constant(4000.0)
-    got = T.vr_rs_time_us(8, m, s, 0.99, T.Policy(adaptive=adaptive), km, 3.0)
+    got = T.vr_rs_time_us(P, m, s, 0.99, T.Policy(adaptive=adaptive), km, 3.0)
     assert got["launches"] == launches
     assert got["launch_us"] == pytest.approx(3.0 * launches)
 
 
 def test_one_gpu_ring_bytes_are_every_rank_summed():
     """Never dense, every op at one bandwidth: the bytes term is the sum over
-    ranks and steps of compress (dense chunk + message), the copy of each
-    received message (read and write) and the reduction (dense chunk, the
-    received message, and the sent message or the dense output at the last
-    step), with the message at sigma0^(k+1) after k + 1 contributions."""
+    ranks and steps of compress (dense chunk + message) and the reduction
+    (dense chunk, the received message, and the sent message, stored in place
+    at the next rank, or the dense output at the last step), with the message
+    at sigma0^(k+1) after k + 1 contributions."""
     P, m, s, sg, GBs = 4, 3 * 4096 + 17, 4, 0.95, 2000.0
     km = T.KernelModel.constant(GBs)
     pici = lambda x: T.message_bytes(m, s, T.FMT_PICI, x)
     total = P * (m * s + pici(sg))
     for step in range(1, P):
         inb = pici(sg ** step)
-        total += P * 2 * inb
         total += P * ((2 * m * s + inb) if step == P - 1 else (m * s + inb + pici(sg ** (step + 1))))
     got = T.vr_rs_time_us(P, m, s, sg, T.Policy(adaptive=0), km, 0.0)
     assert got["bytes_us"] == pytest.approx(total / (GBs * 1e3), rel=1e-12)
