@@ -2509,7 +2509,8 @@ __device__ __forceinline__ void copy_wave(const typename E::raw* src, typename E
 // next one, so only the first and last line of the wave's run are stored in
 // part.  Row-by-row stores of unaligned rows (two part lines per 128-byte
 // row) ran at 0.6 TB/s: a sliced all-gather hop of 8 x 5,000,011 bf16
-// elements took 140 us, now 50 (with block_tiles).
+// elements took 140 us, now 57 (with block_tiles; 71 to 78 where it also
+// writes the stream on).
 template <class E>
 struct LineOut {
     using raw = typename E::raw;
@@ -3746,8 +3747,10 @@ spccl_status_t launch_to_coo_dt(int dtype, int sa, int sb, const PiciSinkArgs& g
 // first store: 256 MiB at 99% then takes 47.4 us instead of 50.5 (at 80%, where
 // the waves do read again, 63 against 53).  Outputs that start inside a line are
 // written in part lines and take the rows up to 128 MiB (80 MiB at 90% 25.1 ->
-// 18.5 us, but 512 MiB at 80% 115 -> 139).  A bf16 row is one line: in whole
-// lines it is the faster at any size.
+// 18.5 us, but 512 MiB at 80% 115 -> 139).  A bf16 row is half as many bytes,
+// and whole lines are the faster (2^27 at 90% 59.1 -> 58.7 us, at 50% 356 -> 119,
+// one element past a line 104 -> 65) but for sliced outputs of 40 to 52 and 72 to
+// 80 MiB, where four waves per SIMD instead of the walk's five cost 5-15%.
 inline bool expand_rows(const uint8_t* out, uint64_t bytes, uint64_t P) {
     const bool whole = ((reinterpret_cast<uintptr_t>(out) | (P > 1 ? bytes : 0)) & 127u) == 0;
     return P * bytes > (64ull << 20) && (whole || P * bytes <= (128ull << 20));

@@ -326,12 +326,19 @@ spccl_status_t ring_ag_batched(void* const* own, void* const* out, int P, uint64
     return SPCCL_OK;
 }
 
+// Ends a collective: waits for it and returns its status.
+spccl_status_t finish(const Layout& L, hipStream_t st) {
+    return spccl_read_status(L.ws, 1, st);
+}
+
 // Ends a device-decided collective: its state and status word come back in one
 // copy, and the sends become trace entries (what: reduce-scatter sends, an
-// all-gather's, or both).
+// all-gather's, or both).  Without a trace only the status does: the state is
+// 32 bytes for each of P * P sends.
 enum TraceOf { kTraceRs = 1, kTraceTransition = 2, kTraceAg = 4 };
 
 spccl_status_t finish_dev(const Layout& L, int P, uint64_t m, int dtype, int what, spccl_trace_t* trace, hipStream_t st) {
+    if (!trace) return finish(L, st);
     std::vector<uint8_t> host(L.row_bytes + sizeof(uint32_t));
     if (hipMemcpyAsync(host.data(), L.rows, host.size(), hipMemcpyDeviceToHost, st) != hipSuccess) return SPCCL_ERR_HIP;
     if (hipStreamSynchronize(st) != hipSuccess) return SPCCL_ERR_HIP;
@@ -339,7 +346,7 @@ spccl_status_t finish_dev(const Layout& L, int P, uint64_t m, int dtype, int wha
     memcpy(&status, host.data() + L.row_bytes, sizeof(status));
     const RingRank* rows = reinterpret_cast<const RingRank*>(host.data());
     const uint64_t dense_bytes = dense_msg_bytes(m, dtype);
-    if ((what & kTraceRs) && trace)
+    if (what & kTraceRs)
         for (int step = 0; step < P - 1; step++)
             for (int r = 0; r < P; r++) {
                 const RingRank& q = rows[(uint64_t)step * P + r];
@@ -348,14 +355,14 @@ spccl_status_t finish_dev(const Layout& L, int P, uint64_t m, int dtype, int wha
                           pici ? pici_bytes(m, dtype, q.nnz) : dense_bytes, counted ? q.nnz : SPCCL_NNZ_UNKNOWN,
                           pici ? sparsity(m, q.nnz) : q.sigma_prev);
             }
-    if ((what & kTraceTransition) && trace)
+    if (what & kTraceTransition)
         for (int r = 0; r < P; r++) {
             const RingRank& q = rows[(uint64_t)(P - 1) * P + r];
             const bool pici = q.fmt == SPCCL_FMT_PICI;
             put_trace(trace, P * (P - 1) + r, P - 1, r, q.fmt, pici ? 1 : 0, pici ? pici_bytes(m, dtype, q.nnz) : dense_bytes,
                       pici ? q.nnz : SPCCL_NNZ_UNKNOWN, q.sigma_prev);
         }
-    if ((what & kTraceAg) && trace)
+    if (what & kTraceAg)
         for (int r = 0; r < P; r++)
             put_trace(trace, r, 0, r, SPCCL_FMT_PICI, 1, pici_bytes(m, dtype, rows[r].nnz), rows[r].nnz,
                       sparsity(m, rows[r].nnz));
@@ -491,10 +498,6 @@ spccl_status_t check_disjoint(void* const* send, uint64_t send_bytes, void* cons
         }
     }
     return SPCCL_OK;
-}
-
-spccl_status_t finish(const Layout& L, hipStream_t st) {
-    return spccl_read_status(L.ws, 1, st);
 }
 
 }  // namespace

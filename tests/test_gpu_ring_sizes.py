@@ -66,3 +66,24 @@ def test_hops_of_two_tiles_forward_dense_tiles(S, td):
         S.spccl_vr_all_gather(parts, out, scratch)
         for r in range(P):
             assert torch.equal(raw(out[r].contiguous()), exp), f"off={off} rank {r}"
+
+
+@pytest.mark.parametrize("adaptive", [0, 1, 2])
+def test_rings_without_a_trace(S, adaptive):
+    """The C calls with no trace array: the same results, and status 0."""
+    import ctypes
+    P, m, dt = 3, 3 * 16384 + 5, S.SPCCL_F32
+    x = [filled(P * m, torch.float32, 40 + r, [0.3, 0.01]) for r in range(P)]
+    pol = S.spccl_policy_t(0.6, 0.5, 0.3, 0, adaptive, S.SPCCL_FMT_PICI)
+    scratch = torch.empty(S.spccl_vr_scratch_bytes(P, P * m, dt), dtype=torch.uint8, device="cuda")
+    ptrs = lambda ts: (ctypes.c_void_p * P)(*[t.data_ptr() for t in ts])
+    for name, n, out in (("reduce_scatter", P * m, m), ("all_gather", m, P * m), ("all_reduce", P * m, P * m)):
+        send = [t[:n] for t in x]
+        got, exp = ([torch.full((out,), 7.0, device="cuda") for _ in range(P)] for _ in range(2))
+        getattr(S, f"spccl_vr_{name}")(send, exp, scratch, pol)
+        st = getattr(S._lib, f"spccl_vr_{name}")(ptrs(send), ptrs(got), P, n, dt, ctypes.byref(pol), scratch.data_ptr(),
+                                                 scratch.numel(), None, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert st == 0
+        for r in range(P):
+            assert torch.equal(raw(got[r]), raw(exp[r])), f"{name} rank {r}"
