@@ -77,6 +77,12 @@ __device__ __forceinline__ uint32_t oplus(BF16, uint32_t a, uint32_t b) {
 // wave primitives
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
 
+// The wave's number in its block, as a scalar: what follows from it (a wave's
+// tiles, its message and its output) then needs no vector registers.
+__device__ __forceinline__ uint32_t wave_index() {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+
 // Inclusive prefix sum over the wave's 64 lanes with DPP moves: shifts by
 // 1, 2, 4, 8 inside each row of 16 lanes (lanes shifted in from outside the
 // row read 0), then each row adds the total of the rows before it (row
@@ -154,8 +160,6 @@ __device__ __forceinline__ void st_stream(uint4* p, uint4 v) {
     const u32x4 x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, reinterpret_cast<u32x4*>(p));
 }
-
-constexpr uint64_t kCacheBytes = 256ull << 20;             // the Infinity Cache
 
 // 16 bytes from any element address (unaligned vector loads).
 template <bool NT>
@@ -315,6 +319,20 @@ __device__ __forceinline__ PiciMeta load_pici_meta(const uint8_t* msg, uint64_t 
     const uint32_t* I = reinterpret_cast<const uint32_t*>(msg + off_I(n));
     return PiciMeta{__builtin_nontemporal_load(&B[t * 64 + lane_id()]), __builtin_nontemporal_load(&I[t]),
                     __builtin_nontemporal_load(&I[t + 1])};
+}
+
+// The same where t is a scalar (see wave_index): the offsets are still read by
+// vector loads.  Scalar loads of them, each waited for with the LDS, took a 2^27
+// bf16 expansion at 90% from 58.8 to 67.4 us; with vector loads the scalar
+// tile index is worth 1-4% (sliced bf16: 123 -> 100 registers).
+template <class E>
+__device__ __forceinline__ PiciMeta load_pici_meta_scalar(const uint8_t* msg, uint64_t t, uint64_t n) {
+    const uint64_t* B = reinterpret_cast<const uint64_t*>(msg + kHeaderBytes);
+    uint32_t zero = 0;
+    asm volatile("" : "+v"(zero));                          // a lane's value, for all the compiler knows
+    const uint32_t* I = reinterpret_cast<const uint32_t*>(msg + off_I(n) + 4 * t + zero);
+    return PiciMeta{__builtin_nontemporal_load(&B[t * 64 + lane_id()]), __builtin_nontemporal_load(&I[0]),
+                    __builtin_nontemporal_load(&I[1])};
 }
 
 // The same through a buffer resource that ends at the message's index
@@ -2638,13 +2656,13 @@ __device__ __forceinline__ void walk_rows(typename E::raw* out, uint32_t rem, ui
     }
 }
 
-// stream: past the caches, where a row is whole lines (part lines written past
-// them are slow: 256 MiB at 99% from one element past a line takes 83 us, and
-// 51 through the caches).
+// Past the caches where a row is whole lines (part lines written past them are
+// slow: 256 MiB at 99% from one element past a line takes 83 us, and 51 through
+// the caches).
 template <class E, int R>
 __device__ __forceinline__ void store_rows(typename E::raw* out, uint32_t rem, uint64_t w, const typename E::raw* stage,
-                                           uint32_t rank, bool stream) {
-    if (stream && (reinterpret_cast<uintptr_t>(out) & (LineOut<E>::kLine - 1)) == 0)
+                                           uint32_t rank) {
+    if ((reinterpret_cast<uintptr_t>(out) & (LineOut<E>::kLine - 1)) == 0)
         walk_rows<E, true, R>(out, rem, w, stage, rank);
     else
         walk_rows<E, false, R>(out, rem, w, stage, rank);
@@ -2745,7 +2763,7 @@ __device__ __forceinline__ void block_tiles(const DenseTiles<E, K>& d, ExpandLds
                 const uint32_t left = rem - e0 < 1024u ? rem - e0 : 1024u;
                 if constexpr (Rows) {
                     store_rows<E, 16>(out + e0, left, w >> (16 * wave), pool,
-                                      pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)), true);
+                                      pref + (uint32_t)__popcll(w & ((1ull << (16 * wave)) - 1ull)));
                 } else {
                     LineOut<E> run;
                     run.start(lds.lines(wave), out + e0);
@@ -2811,13 +2829,12 @@ __device__ __forceinline__ void coo_tiles_lds(const uint32_t* J, const typename 
 // forwarded: the message itself (Pici or dense) is also written there, each
 // wave its tiles' parts, while it is at hand (an all-gather hop used to copy
 // the message first and then read the copy).  One wave; all reads before the
-// first store (see k_gather).  Rows: tiles are stored row by row, past the
-// caches unless cached is set and no read is waited for after the stores.
+// first store (see k_gather).  Rows: tiles are stored row by row.
 template <class E, int K, bool Rows>
 __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* d, uint32_t fmt, uint64_t nnz,
                                              uint64_t n, uint64_t T, uint64_t t0, typename E::raw* out,
                                              typename E::raw* stage, uint4* lines, WsCtrl* ctrl,
-                                             DenseTiles<E, K>& dense, uint8_t* fwd, bool cached) {
+                                             DenseTiles<E, K>& dense, uint8_t* fwd) {
     using raw = typename E::raw;
     const uint32_t l = lane_id();
     const uint64_t g_n = n, g_T = T;
@@ -2865,7 +2882,7 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
     PiciMeta m[K];
 #pragma unroll
     for (int k = 0; k < K; k++)
-        m[k] = t0 + k < g_T ? load_pici_meta<E>(msg, t0 + k, g_n) : PiciMeta{0, 0, 0};
+        m[k] = t0 + k < g_T ? load_pici_meta_scalar<E>(msg, t0 + k, g_n) : PiciMeta{0, 0, 0};
     uint64_t cw[K];
     uint32_t cpref[K], ccnt[K], cbase[K];
     int kfit = 0;                       // leading tiles whose values are staged together
@@ -2936,7 +2953,7 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
             }
             if constexpr (Rows) {
                 store_rows<E, 64>(out + t * kTileElems, (uint32_t)(rem < kTileElems ? rem : kTileElems), w, stage,
-                                  k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k], !(cached && kfit == K));
+                                  k < kfit ? (cbase[k] - cbase[0]) + cpref[k] : cpref[k]);
             } else {
                 if (!running) run.start(lines, out + t * kTileElems);
                 const bool last = k + 1 == K || t + 1 >= g_T || ccnt[k + 1 < K ? k + 1 : k] > kChunkVals;
@@ -2971,12 +2988,12 @@ __device__ __forceinline__ void expand_tiles(const uint8_t* msg, const uint8_t* 
 // kChunkVals values by the whole block (block_tiles).
 template <class E, int K, bool Rows>
 __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_part, uint64_t n, uint64_t T,
-                                            WsCtrl* ctrl, uint8_t* fwd, bool cached) {
+                                            WsCtrl* ctrl, uint8_t* fwd) {
     using raw = typename E::raw;
     __shared__ ExpandLds<E, Rows> lds;
     __shared__ uint32_t s_ok, s_fmt;
     __shared__ uint64_t s_nnz;
-    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t wave = wave_index();
     if (threadIdx.x == 0) {
         if (op.hdr) {
             HeaderView h = read_header(op.hdr, op.cap, n, E::dtype, -1);
@@ -2993,23 +3010,22 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
     const uint8_t* d = op.hdr ? op.hdr + kHeaderBytes : op.data;
     DenseTiles<E, K> dense{};
     if (t0 < T)
-        expand_tiles<E, K, Rows>(op.data, d, s_fmt, s_nnz, n, T, t0, out, lds.stage[wave], lds.lines(wave), ctrl, dense,
-                                 fwd, cached);
+        expand_tiles<E, K, Rows>(op.data, d, s_fmt, s_nnz, n, T, t0, out, lds.stage[wave], lds.lines(wave), ctrl, dense, fwd);
     block_tiles<E, K, Rows>(dense, lds);
 }
 
-// Pairs of tiles are held to five waves per SIMD where that spills nothing: bf16,
-// and fp32 stored row by row (94 registers; 100 ran four waves: two fp32 parts of
-// 68 MiB at 70% 47 -> 34 us).  A bf16 tile per wave takes 92 by itself, the LDS of
-// fp32 in whole lines fits four, and the sliced kernels spill at five (2^27 bf16
-// at 90% 58.6 -> 64.1 us).
+// Pairs of tiles are held to five waves per SIMD: bf16, and fp32 stored row by
+// row (94 registers; 100 ran four waves: two fp32 parts of 68 MiB at 70% 47 -> 34
+// us).  A bf16 tile per wave takes 92 by itself, and the LDS of fp32 in whole
+// lines fits four.  The sliced kernels stay at four (100 registers): five took 72
+// to 80 MiB of bf16 at 90% from 21.2 to 18.3 us, but 96 MiB from 23.2 to 24.7 (28.6
+// to 31.7 cold).
 constexpr int expand_waves(size_t s, int K, bool rows) { return rows || (s == 2 && K == 2) ? 5 : 1; }
 
 template <class E, int K, bool Rows>
 __global__ void __launch_bounds__(kBlockThreads, expand_waves(sizeof(typename E::raw), K, Rows)) k_gather(GatherArgs g) {
-    const uint64_t part = g.n * sizeof(typename E::raw);
-    gather_body<E, K, Rows>(g.part[blockIdx.y], g.out + blockIdx.y * part, g.n, g.T, g.ctrl, nullptr,
-                            gridDim.y * part <= kCacheBytes);
+    gather_body<E, K, Rows>(g.part[blockIdx.y], g.out + (uint64_t)blockIdx.y * g.n * sizeof(typename E::raw), g.n, g.T,
+                            g.ctrl, nullptr);
 }
 
 // One all-gather hop for a batch of ranks (grid y): each rank expands the
@@ -3018,7 +3034,7 @@ __global__ void __launch_bounds__(kBlockThreads, expand_waves(sizeof(typename E:
 template <class E, int K>
 __global__ void __launch_bounds__(kBlockThreads) k_gather_rb(DevOperand part, uint64_t n, WsCtrl* ctrl, RankBatch rb) {
     gather_body<E, K, false>(rebase(part, rb.a[blockIdx.y]), rb.out[blockIdx.y], n, num_tiles(n), ctrl,
-                             rb.slots[blockIdx.y], false);
+                             rb.slots[blockIdx.y]);
 }
 
 // ---------------------------------------------------------------------------
@@ -3194,7 +3210,7 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
     using raw = typename E::raw;
     constexpr uint32_t K = kTilesPerPart / kExpandWavesPerSlice;
     __shared__ ExpandLds<E, Rows> lds;
-    const uint32_t wave = threadIdx.x >> 6;
+    const uint32_t wave = wave_index();
     const uint64_t wq = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
     const uint64_t q = wq / kExpandWavesPerSlice, t0 = K * (wq % kExpandWavesPerSlice);
     const uint64_t base = q * kSliceElems;
@@ -3209,7 +3225,7 @@ __device__ __forceinline__ void expand_slice(const SlicedArgs& g) {
             } else {
                 expand_tiles<E, K, Rows>(bm, bm + kHeaderBytes, h.fmt, h.nnz, ns, num_tiles(ns), t0,
                                          reinterpret_cast<raw*>(g.out) + base, lds.stage[wave], lds.lines(wave), g.ctrl,
-                                         dense, Forward && g.fwd ? g.fwd + q * g.slot : nullptr, g.n * sizeof(raw) <= kCacheBytes);
+                                         dense, Forward && g.fwd ? g.fwd + q * g.slot : nullptr);
             }
         }
     }
@@ -3278,6 +3294,7 @@ __global__ void __launch_bounds__(kBlockThreads) k_copy_sliced(SlicedArgs g, uin
 // holds, operands are read non-temporally (256 MiB sums 138 -> 124 us); below,
 // ordinary loads find what the previous call left there.
 constexpr uint64_t kSumChunk = 16384, kCopyChunk = 4096;   // bytes of output per block
+constexpr uint64_t kCacheBytes = 256ull << 20;             // the Infinity Cache
 
 __device__ __forceinline__ u32x4 oplus_vec(F32, u32x4 x, u32x4 y) {
     u32x4 z;
@@ -3741,19 +3758,19 @@ spccl_status_t launch_to_coo_dt(int dtype, int sa, int sb, const PiciSinkArgs& g
 // double a block's LDS: four blocks fit a CU, 1024 the chip, which is 64 MiB at
 // a tile per wave.  Up to there lines are as fast or faster (16 MiB at 99%, cold
 // 10.2 us against 11.6; sliced, 32 MiB 10.5 against 12.6); beyond, the rows are
-// (80 MiB at 90% 23.4 -> 18.0 us, 256 MiB at 99% 52.2 -> 48.0, sliced 55.0 ->
-// 45.5, 512 MiB at 90% 105.8 -> 101).  They leave the chip past the caches,
-// unless the output fits the Infinity Cache and no wave reads again after its
-// first store: 256 MiB at 99% then takes 47.4 us instead of 50.5 (at 80%, where
-// the waves do read again, 63 against 53).  Outputs that start inside a line are
-// written in part lines and take the rows up to 128 MiB (80 MiB at 90% 25.1 ->
-// 18.5 us, but 512 MiB at 80% 115 -> 139).  A bf16 row is half as many bytes,
-// and whole lines are the faster (2^27 at 90% 59.1 -> 58.7 us, at 50% 356 -> 119,
-// one element past a line 104 -> 65) but for sliced outputs of 40 to 52 and 72 to
-// 80 MiB, where four waves per SIMD instead of the walk's five cost 5-15%.
+// (80 MiB at 90% 23.4 -> 18.4 us, 256 MiB at 99% 52.2 -> 50.5, sliced 55.2 ->
+// 50.6, 512 MiB at 90% 105.8 -> 101).  Rows stored through the caches would be
+// faster still into one buffer again and again (256 MiB at 99% 47 us), but among
+// other buffers slower: compress and expand 200 MiB at 90%, sliced, 84.6 us past
+// them and 94.8 through them.  Outputs that start inside a line are written in
+// part lines, through the caches, and take the rows up to 96 MiB (80 MiB at 90%
+// 25.1 -> 18.5 us, but 512 MiB at 80% 115 -> 139).  A bf16 row is half as many
+// bytes, and whole lines are the faster (2^27 at 90% 59.1 -> 58.7 us, at 50% 356
+// -> 119, one element past a line 104 -> 65) but for sliced outputs around 48 and
+// 76 MiB, where four waves per SIMD instead of the walk's five cost up to 10%.
 inline bool expand_rows(const uint8_t* out, uint64_t bytes, uint64_t P) {
     const bool whole = ((reinterpret_cast<uintptr_t>(out) | (P > 1 ? bytes : 0)) & 127u) == 0;
-    return P * bytes > (64ull << 20) && (whole || P * bytes <= (128ull << 20));
+    return P * bytes > (64ull << 20) && (whole || P * bytes <= (96ull << 20));
 }
 
 // Tiles per wave of an expansion: two where that still leaves more waves than
@@ -3761,7 +3778,10 @@ inline bool expand_rows(const uint8_t* out, uint64_t bytes, uint64_t P) {
 // 10% slower at 90% (their values no longer fit one staged chunk), one 5-10%
 // slower at 99%.  bf16 also takes two where one would run the chip's waves a
 // little more than once: 48 MiB at 99% 15.4 -> 12.9 us, 90% 15.7 -> 13.8 (but 96
-// MiB at 50%, two rounds of pairs, 49.8 -> 60).  Rows of fp32 always take two.
+// MiB at 50%, two rounds of pairs, 49.8 -> 60).  Rows of fp32 always take two; from
+// 128 MiB to where lines take two as well, they stay lines: with pairs 164 MiB
+// took 13-20% less at 95-99% on buffers in the caches, but on other buffers 5%
+// more at 88% and 10% more at 50%.
 constexpr uint64_t kResidentWaves = 5 * 1024;      // five per SIMD
 
 template <class E>
@@ -3770,11 +3790,13 @@ void launch_gather_k(const GatherArgs& g, int P, hipStream_t st) {
     dim3 block(kBlockThreads);
     auto grid = [&](uint32_t K) { return dim3(stream_grid(g.T, kWavesPerBlock * K, 0x7FFFFFFF), (unsigned)P); };
     if constexpr (sizeof(typename E::raw) == 4) {
-        if (expand_rows(g.out, g.n * sizeof(typename E::raw), (uint64_t)P)) {
+        const uint64_t part = g.n * sizeof(typename E::raw);
+        const bool two = tiles >= 2 * 8192;
+        if (expand_rows(g.out, part, (uint64_t)P) && (two || P * part <= (128ull << 20))) {
             hipLaunchKernelGGL((k_gather<E, 2, true>), grid(2), block, 0, st, g);
             return;
         }
-        if (tiles >= 2 * 8192) hipLaunchKernelGGL((k_gather<E, 2, false>), grid(2), block, 0, st, g);
+        if (two) hipLaunchKernelGGL((k_gather<E, 2, false>), grid(2), block, 0, st, g);
         else hipLaunchKernelGGL((k_gather<E, 1, false>), grid(1), block, 0, st, g);
     } else {
         const bool two = tiles >= 2 * 8192 || (tiles > kResidentWaves && tiles <= 2 * kResidentWaves);

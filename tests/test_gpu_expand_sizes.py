@@ -1,7 +1,7 @@
 """The expansion where its launch changes form with the size: fp32 outputs above
 64 MiB (rows stored as they are walked) with tiles of every density side by
-side, aligned to a line and not, either side of 128 MiB (unaligned outputs go
-back to whole lines) and of 256 MiB (the rows' stores change), from one message,
+side, aligned to a line and not, either side of 96 MiB (unaligned outputs go
+back to whole lines) and of 128 and 256 MiB (all do, in between), from one message,
 several parts, COO, dense and sliced streams; bf16 where a pair of tiles per
 wave replaces one.  Whole outputs bit for bit, and the elements around them."""
 import pytest
@@ -15,9 +15,9 @@ torch = pytest.importorskip("torch")
 
 MIX = [0.01, 0.1, 0.2495, 0.2505, 0.0, 0.6, 0.01, 1.0, 0.5, 0.12, 0.13]
 MIB_F32, MIB_BF16 = 1 << 18, 1 << 19
-# fp32: 64 MiB (lines), one element more, a tile more, 128 MiB and a little more, 256 MiB and a little more
-CASES = [(torch.float32, n) for n in (64 * MIB_F32, 64 * MIB_F32 + 1, 64 * MIB_F32 + 4097, 128 * MIB_F32 + 3,
-                                      256 * MIB_F32 + 5)]
+# fp32: 64 MiB (lines), one element more, a tile more, 96, 128 and 256 MiB and a little more
+CASES = [(torch.float32, n) for n in (64 * MIB_F32, 64 * MIB_F32 + 1, 64 * MIB_F32 + 4097, 96 * MIB_F32, 96 * MIB_F32 + 1,
+                                      128 * MIB_F32, 128 * MIB_F32 + 3, 256 * MIB_F32 + 5)]
 # bf16: 5120 tiles (one per wave), one more (pairs), 10240 (pairs) and one more (one per wave)
 CASES += [(torch.bfloat16, 4096 * t - 7) for t in (5120, 5121, 10240, 10241)]
 
