@@ -3015,9 +3015,9 @@ __device__ __forceinline__ void gather_body(const DevOperand& op, uint8_t* out_p
 }
 
 // Pairs of tiles are held to five waves per SIMD: bf16, and fp32 stored row by
-// row (94 registers; 100 ran four waves: two fp32 parts of 68 MiB at 70% 47 -> 34
-// us).  A bf16 tile per wave takes 92 by itself, and the LDS of fp32 in whole
-// lines fits four.  The sliced kernels stay at four (100 registers): five took 72
+// row (94 registers; 100 ran four waves: compress and expand 2^26 fp32 at 99%
+// 107.8 -> 107.3 us).  A bf16 tile per wave takes 92 by itself, and the LDS of fp32
+// in whole lines fits four.  The sliced kernels stay at four (100 registers): five took 72
 // to 80 MiB of bf16 at 90% from 21.2 to 18.3 us, but 96 MiB from 23.2 to 24.7 (28.6
 // to 31.7 cold).
 constexpr int expand_waves(size_t s, int K, bool rows) { return rows || (s == 2 && K == 2) ? 5 : 1; }
@@ -3778,10 +3778,10 @@ inline bool expand_rows(const uint8_t* out, uint64_t bytes, uint64_t P) {
 // 10% slower at 90% (their values no longer fit one staged chunk), one 5-10%
 // slower at 99%.  bf16 also takes two where one would run the chip's waves a
 // little more than once: 48 MiB at 99% 15.4 -> 12.9 us, 90% 15.7 -> 13.8 (but 96
-// MiB at 50%, two rounds of pairs, 49.8 -> 60).  Rows of fp32 always take two; from
-// 128 MiB to where lines take two as well, they stay lines: with pairs 164 MiB
-// took 13-20% less at 95-99% on buffers in the caches, but on other buffers 5%
-// more at 88% and 10% more at 50%.
+// MiB at 50%, two rounds of pairs, 49.8 -> 60).  Rows of fp32 always take two, so
+// from 128 MiB to where lines take two as well lines stay: compress and expand
+// 164 MiB at 88% 81.0 us in lines and 82.6 in pairs of rows, at 50% after a large
+// write 160 and 174 (at 95-99% within 1%).
 constexpr uint64_t kResidentWaves = 5 * 1024;      // five per SIMD
 
 template <class E>
